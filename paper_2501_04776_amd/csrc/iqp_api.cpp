@@ -329,6 +329,9 @@ void make_plan(Plan &P, const PlanParts &parts, int64_t n, int64_t m, int64_t l,
         } else {
             P.o_s32 = carve(cur, (size_t)P.s_pad * P.l_pad * 4);
         }
+        // gate lists: counters and two entry arrays per 64 observables
+        P.o_gcnt = carve(cur, (size_t)P.lw * 4 * 4);
+        P.o_glist = carve(cur, (size_t)P.lw * 2 * P.m_pad * 4);
         P.o_gpart = carve(cur, (size_t)P.tc.bsplits * (P.l_pad / (32 * P.tc.bfm)) * P.m_pad * 4);
     }
     if (P.mmd) {
@@ -570,10 +573,11 @@ static int run_backward(const Plan &P, const iqp_circuit *c, const uint64_t *ops
         IQP_TRY(launch_bitslice(lc, bitslice_ops_args(P, ops, ws)), "bitslice(A)");
         IQP_TRY(launch_bitslice(lc, bitslice_samples_args(P, samples, ws)), "bitslice(Z)");
     }
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32_T, parity_bt_args(P, c->gens, ws)),
+    IQP_TRY(launch_parity_bs(lc, kBitsWordMajor, parity_bt_args(P, c->gens, ws)),
             "parity(B^T)");
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32_T, parity_ct_args(P, c->gens, ws)),
+    IQP_TRY(launch_parity_bs(lc, kBitsWordMajor, parity_ct_args(P, c->gens, ws)),
             "parity(C^T)");
+    IQP_TRY(launch_gate_list(lc, gate_list_args(P, ws, P.tc.bfm, P.tc.bfn)), "gate_list");
     IQP_TRY(launch_phase_bwd(lc, P.prec, P.tc.bfm, P.tc.bfn, bwd_args(P, ws)), "phase_bwd");
     IQP_TRY(launch_grad_reduce(lc, grad_args(P, ws, P.tc.bfm, grad_theta)), "grad_reduce");
     return IQP_OK;
@@ -839,7 +843,7 @@ int iqp_mmd_loss_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops,
     if (!grad_theta) return IQP_OK;
     const CoefArgs ca = coef_args(P, nullptr, ws);
     IQP_TRY(launch_coef_mmd(lc, at<double>(ws, P.o_pstat), at<double>(ws, P.o_rowsum), op_weight,
-                            l, s, unbiased, ca.coef, ca.sq, ca.nf),
+                            l, s, unbiased, ca.coef, ca.sq, ca.nf, ca.gcnt, ca.n_gcnt),
             "coef_mmd");
     return run_backward(P, c, ops, samples, phi, true, ws, lc, grad_theta);
 }

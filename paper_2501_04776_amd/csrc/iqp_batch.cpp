@@ -279,13 +279,16 @@ static void build_table(const iqp_batch_plan *bp, int pass, const iqp_problem *p
         std::vector<CoefArgs> co;
         std::vector<WeightsArgs> we;
         std::vector<GradArgs> gr;
-        std::vector<int64_t> con, wen, grn;
+        std::vector<GateListArgs> gl;
+        std::vector<int64_t> con, wen, grn, gln;
         for (int p = 0; p < np; ++p) {
             const Plan &P = bp->plans[p];
             const iqp_problem *q = pr(p);
             co.push_back(coef_args(P, q ? q->grad_mean : nullptr, base(p)));
             we.push_back(weights_args(P, q ? q->phase_save : nullptr, base(p)));
             gr.push_back(grad_args(P, base(p), c.bfm, q ? q->grad_theta : nullptr));
+            gl.push_back(gate_list_args(P, base(p), c.bfm, c.bfn));
+            gln.push_back(blocks_of(gl.back()));
             con.push_back(blocks_of(co.back()));
             wen.push_back(blocks_of(we.back()));
             grn.push_back(blocks_of(gr.back()));
@@ -297,13 +300,14 @@ static void build_table(const iqp_batch_plan *bp, int pass, const iqp_problem *p
         std::vector<int64_t> bwn;
         for (int p : order) {
             bw.push_back(bwd_args(bp->plans[p], base(p)));
-            bwn.push_back(bwd_units(bw.back(), c.bfm, c.bfn));
+            bwn.push_back(bwd_units(bw.back(), bp->prec, c.bfm, c.bfn));
         }
         tb.add(SK_COEF, co, con);
         tb.add(SK_WEIGHTS, we, wen);
         tb.add(SK_SUPPORT, su, sun);
         tb.add(SK_BITSLICE, bs, bsn);
-        tb.add(SK_PARITY2, par, parn);
+        tb.add(SK_PARITY4, par, parn);
+        tb.add(SK_GATELIST, gl, gln);
         tb.add(SK_BWD_PERSISTENT, bw, bwn);
         tb.add(SK_GRAD, gr, grn);
     }

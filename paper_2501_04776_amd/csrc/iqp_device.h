@@ -86,8 +86,9 @@ __global__ __launch_bounds__(256) void plain_kernel(A a) {
 
 template <typename A, void (*F)(const A &, int64_t)>
 __global__ __launch_bounds__(256) void batched_kernel(const A *__restrict__ args,
-                                                      const int64_t *__restrict__ off, int np) {
-    const int64_t b = (int64_t)blockIdx.x;
+                                                      const int64_t *__restrict__ off, int np,
+                                                      int64_t base) {
+    const int64_t b = base + (int64_t)blockIdx.x;
     const int p = find_slot(off, np, b);
     const A a = args[p];
     F(a, b - off[p]);

@@ -29,7 +29,7 @@ struct TileCfg {
     int bfm = 2, bfn = 2;    // backward: observables x gates
     int64_t splits = 0;      // forward split over gate words; 0 = choose
     int64_t bsplits = 0;     // backward split over sample words; 0 = choose
-    int64_t obgroup = 4;     // backward unit order: observable blocks per group
+    int64_t obgroup = 8;     // backward unit order: observable blocks per group
 };
 
 // Kernel-family ids for the optional per-kernel timing.
@@ -105,9 +105,11 @@ inline int64_t blocks_of(const SupportArgs &a) { return ceil_div(a.rows, 256); }
 
 // Parity of each generator (m of them, W words each, support lists `sup`
 // covering 64 Gw rows) against the rows behind Xt (Rw words of 64 rows), in
-// layout 0 (row-major), 1 (tiled32) or 2 (transposed tiled32); Gw = output
-// words per row in layouts 0/1, generator words in layout 2. One wave per 64
+// layout 0 (row-major), 1 (tiled32), 2 (transposed tiled32), 3 (transposed
+// row-major) or 4 (transposed word-major); Gw = output words per row in
+// layouts 0/1, generator words in the others. One wave per 64
 // generators x 64 row words.
+constexpr int kBitsWordMajor = 4;
 struct ParityArgs {
     const uint64_t *gens;
     const int32_t *sup;
@@ -150,13 +152,16 @@ inline int64_t blocks_of(const FinArgs &a) { return ceil_div(a.l, 256); }
 // coef[2k], coef[2k+1] = alpha_k, beta_k of the backward weights. For the
 // fixed-point weights (IQP_SPLIT3_BF16) also the row scale
 // sq[k] = (|alpha_k| + |beta_k|) / kI8Max and a zeroed non-finite flag nf[k];
-// both pointers are NULL for the other forms.
+// both pointers are NULL for the other forms. gcnt (NULL in the sparse form):
+// n_gcnt counters of the gate lists, zeroed.
 struct CoefArgs {
     const double *grad_mean;
     int64_t l, s;
     double *coef;
     double *sq;
     int32_t *nf;
+    int32_t *gcnt;
+    int64_t n_gcnt;
 };
 inline int64_t blocks_of(const CoefArgs &a) { return ceil_div(a.l, 256); }
 
@@ -177,10 +182,34 @@ struct WeightsArgs {
 };
 inline int64_t blocks_of(const WeightsArgs &a) { return (a.s_pad / 64) * (a.l_pad / 64); }
 
-// T = S B (observables x gates, K = samples, split `ksplits` ways over the
-// sample words) and the gradient partials gpart[ksplits][l_pad / (32 fm)][m_pad];
-// btbits / ctbits are the transposed tiled32 parities of the samples /
-// observables against the generators. Every split must hold >= 1 sample word.
+// Gate lists of the backward. A block of 32 cf observables contributes to the
+// gradient of gate j only if some observable of the block anticommutes with
+// j, so the contraction runs over the listed gates of each block. A gate is
+// listed by the halves of the block (cf / 2 fragments of 32 rows each) that
+// hold such an observable: both (class 0), the lower only (class 1), the
+// upper only (class 2). gcnt[ob * 4 + class] counts; with one class array
+// (`split` 0) every listed gate is in class 0. Entries of class 0 at
+// glist[(ob * 2) * m_pad + i], of class 1 at glist[(ob * 2 + 1) * m_pad + i],
+// of class 2 at the end of that array, glist[(ob * 2 + 2) * m_pad - 1 - i].
+// The order of a list varies from run to run; no result depends on it, since
+// every gate is a column of its own in the product.
+struct GateListArgs {
+    const uint64_t *ctbits;
+    int64_t m, m_pad, lw;
+    int cw;     // 64-row words per block: cf / 2
+    int split;  // classes by half (1) or one class (0)
+    int32_t *gcnt, *glist;
+};
+constexpr int64_t kListSeg = 1024;  // gates per block of the list kernel
+inline int64_t blocks_of(const GateListArgs &a) {
+    return (a.lw / a.cw) * ceil_div(a.m_pad, kListSeg);
+}
+
+// T = S B (observables x listed gates, K = samples, split `ksplits` ways over
+// the sample words) and the gradient partials gpart[ksplits][n_ob][m_pad],
+// n_ob = l_pad / (32 cf), written for the listed gates of each block only;
+// btbits / ctbits are the transposed word-major parities of the samples /
+// observables against the generators (word w of gate j at [w * m_pad + j]). Every split must hold >= 1 sample word.
 struct BwdArgs {
     const uint16_t *shi, *slo;
     const float *s32;
@@ -191,17 +220,36 @@ struct BwdArgs {
                         // non-finite flags (IQP_SPLIT3_BF16)
     const int32_t *nf;
     int64_t obgroup;    // observable blocks per unit group (unit order only)
+    const int32_t *gcnt, *glist;
 };
-inline int64_t bwd_units(const BwdArgs &a, int fm, int fn) {
-    return ceil_div(a.m_pad / (32 * fn), 4) * (a.l_pad / (32 * fm)) * a.ksplits;
+// How the backward of a form runs its tile configuration bfm x bfn: gates of a
+// wave in column blocks of 32 (fn), and whether the lists are split by the
+// halves of a block of 32 bfm observables.
+struct BwdShape {
+    int fn;
+    bool split;
+};
+BwdShape bwd_shape(int prec, int bfm, int bfn);
+// Workgroup tiles over one block's gate lists: room for every gate, and for
+// the partly filled last tile of each further class.
+__host__ __device__ inline int64_t bwd_list_tiles(int64_t m_pad, int fn, bool split) {
+    return ceil_div(m_pad, 128 * fn) + (split ? 2 : 0);
+}
+inline int64_t bwd_units(const BwdArgs &a, int prec, int bfm, int bfn) {
+    const BwdShape sh = bwd_shape(prec, bfm, bfn);
+    return bwd_list_tiles(a.m_pad, sh.fn, sh.split) * (a.l_pad / (32 * bfm)) * a.ksplits;
 }
 
+// n_parts = ksplits n_ob partials per gate, block ob of 64 cw rows present
+// only where one of its C^T words is non-zero.
 struct GradArgs {
     const float *gpart;
-    int64_t n_parts, m, m_pad;
+    int64_t n_ob, ksplits, m, m_pad;
     double *grad;
+    const uint64_t *ctbits;
+    int cw;
 };
-inline int64_t blocks_of(const GradArgs &a) { return ceil_div(a.m, 256); }
+inline int64_t blocks_of(const GradArgs &a) { return ceil_div(a.m, 64); }
 
 // Stochastic bitflip circuits (exact product form).
 struct BitflipPrepArgs {
@@ -310,6 +358,7 @@ hipError_t launch_epilogue(const LaunchCtx &lc, const EpiArgs &a);
 hipError_t launch_finalize(const LaunchCtx &lc, const FinArgs &a);
 hipError_t launch_coef_plain(const LaunchCtx &lc, const CoefArgs &a);
 hipError_t launch_weights(const LaunchCtx &lc, const WeightsArgs &a);
+hipError_t launch_gate_list(const LaunchCtx &lc, const GateListArgs &a);
 hipError_t launch_phase_bwd(const LaunchCtx &lc, int prec, int fm, int fn, const BwdArgs &a);
 hipError_t launch_grad_reduce(const LaunchCtx &lc, const GradArgs &a);
 hipError_t launch_sparse_fwd(const LaunchCtx &lc, const SparseFwdArgs &a);
@@ -325,8 +374,8 @@ hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a);
 // step's type and `off` a device array of np + 1 prefix sums of their block
 // counts (off[0] = 0, off[np] = total > 0).
 enum StepKind {
-    SK_THETA = 0, SK_BITSLICE, SK_PARITY0, SK_PARITY1, SK_PARITY2, SK_EPI, SK_FIN, SK_COEF,
-    SK_WEIGHTS, SK_GRAD, SK_SUPPORT, SK_COUNT
+    SK_THETA = 0, SK_BITSLICE, SK_PARITY0, SK_PARITY1, SK_PARITY4, SK_EPI, SK_FIN, SK_COEF,
+    SK_WEIGHTS, SK_GRAD, SK_SUPPORT, SK_GATELIST, SK_COUNT
 };
 hipError_t launch_batched(const LaunchCtx &lc, int kind, const void *args, const int64_t *off,
                           int np, int64_t total);
@@ -357,6 +406,6 @@ hipError_t launch_mmd_loss(const LaunchCtx &lc, const double *pstat, const doubl
 
 hipError_t launch_coef_mmd(const LaunchCtx &lc, const double *pstat, const double *rowsum,
                            const double *op_weight, int64_t l, int64_t s, int unbiased,
-                           double *coef, double *sq, int32_t *nf);
+                           double *coef, double *sq, int32_t *nf, int32_t *gcnt, int64_t n_gcnt);
 
 }  // namespace iqp

@@ -74,6 +74,7 @@ struct Plan {
     size_t o_btbits = 0;                  // B^T: samples against generators, transposed
     size_t o_sup = 0;                     // support lists of the generators
     size_t o_enc = 0, o_stat = 0;         // bitflip circuits: factors, per-observable sums
+    size_t o_gcnt = 0, o_glist = 0;       // gate lists of the backward
     size_t o_acc = 0, o_scale = 0;        // sparse gradient: int64 sums (+ flag), scale
     int64_t ldz = 0, lda = 0;
     size_t total = 0;
@@ -135,7 +136,7 @@ inline ParityArgs parity_b_args(const Plan &P, const uint64_t *gens, void *ws) {
                       at<uint64_t>(ws, P.o_xz), P.s_pad / 64, P.ldz, P.s_pad,
                       P.mw,    at<uint64_t>(ws, P.o_bbits)};
 }
-// B^T and C^T (transposed tiled32) for the backward
+// B^T and C^T (transposed word-major) for the backward
 inline ParityArgs parity_bt_args(const Plan &P, const uint64_t *gens, void *ws) {
     return ParityArgs{gens,    at<int32_t>(ws, P.o_sup), P.m,   (int)P.W,
                       at<uint64_t>(ws, P.o_xz), P.s_pad / 64, P.ldz, 0,
@@ -163,8 +164,10 @@ inline FinArgs fin_args(const Plan &P, void *ws, double *mean, double *se, doubl
 }
 inline CoefArgs coef_args(const Plan &P, const double *grad_mean, void *ws) {
     const bool fx = P.prec == IQP_SPLIT3_BF16;
+    const bool dense = P.o_glist != 0;
     return CoefArgs{grad_mean, P.l, P.s, at<double>(ws, P.o_coef),
-                    fx ? at<double>(ws, P.o_sq) : nullptr, fx ? at<int32_t>(ws, P.o_nf) : nullptr};
+                    fx ? at<double>(ws, P.o_sq) : nullptr, fx ? at<int32_t>(ws, P.o_nf) : nullptr,
+                    dense ? at<int32_t>(ws, P.o_gcnt) : nullptr, dense ? 4 * P.lw : 0};
 }
 inline WeightsArgs weights_args(const Plan &P, const float *phase, void *ws) {
     return WeightsArgs{phase,  at<double>(ws, P.o_coef), P.l, P.s, P.l_pad, P.s_pad, P.prec,
@@ -183,11 +186,25 @@ inline BwdArgs bwd_args(const Plan &P, void *ws) {
                    P.tc.bsplits,                 at<float>(ws, P.o_gpart),
                    rs ? at<double>(ws, P.o_sq) : nullptr,
                    fx ? at<int32_t>(ws, P.o_nf) : nullptr,
-                   P.tc.obgroup};
+                   P.tc.obgroup,
+                   at<int32_t>(ws, P.o_gcnt),
+                   at<int32_t>(ws, P.o_glist)};
+}
+inline GateListArgs gate_list_args(const Plan &P, void *ws, int bfm, int bfn) {
+    return GateListArgs{at<uint64_t>(ws, P.o_ctbits), P.m,
+                        P.m_pad,                      P.lw,
+                        bfm / 2,                      bwd_shape(P.prec, bfm, bfn).split ? 1 : 0,
+                        at<int32_t>(ws, P.o_gcnt),    at<int32_t>(ws, P.o_glist)};
 }
 inline GradArgs grad_args(const Plan &P, void *ws, int bfm, double *grad_theta) {
-    return GradArgs{at<float>(ws, P.o_gpart), P.tc.bsplits * (P.l_pad / (32 * bfm)), P.m, P.m_pad,
-                    grad_theta};
+    return GradArgs{at<float>(ws, P.o_gpart),
+                    P.l_pad / (32 * bfm),
+                    P.tc.bsplits,
+                    P.m,
+                    P.m_pad,
+                    grad_theta,
+                    at<uint64_t>(ws, P.o_ctbits),
+                    bfm / 2};
 }
 
 }  // namespace iqp
