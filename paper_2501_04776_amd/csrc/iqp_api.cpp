@@ -515,6 +515,64 @@ static int run_sparse_parities(const Plan &P, const iqp_circuit *c, const uint64
     return IQP_OK;
 }
 
+// The FP32 forward asks for the non-zero entries of C from this many terms
+// l s m on: below, the dense product takes less than the launches that decide
+// (2^31 terms: about 35 us of matrix cores against 10 us for the count and the
+// kernels that leave at once).
+constexpr double kChainTerms = 2147483648.0;
+// It goes over the non-zero entries up to this share of them: the matrix cores
+// take 6e13 terms/s, whatever C holds, when their wave tiles fill the chip, the
+// other way 5 to 7e12 non-zero terms/s at any size. Where the tiles leave wave
+// slots empty the line moves up, to at most a third (256 observables, 4096
+// samples, 20000 gates: 1.74 ms of matrix cores on 192 of 1024 slots, 0.23 ms
+// for 7.7 % non-zero).
+static double chain_density(const Plan &P) {
+    const int64_t tiles = (P.l_pad / (32 * P.tc.fm)) * (P.s_pad / (32 * P.tc.fn)) * P.tc.splits;
+    const double fill = (double)tiles / (double)(ceil_div(tiles, kWaveSlots) * kWaveSlots);
+    const double d = 1.0 / (12.0 * fill);
+    return d < 1.0 / 3.0 ? d : 1.0 / 3.0;
+}
+
+static int run_forward_fp32(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
+                            const uint64_t *samples, void *ws, const LaunchCtx &lc,
+                            float *phase_out, double *mean, double *se, double *rowsum) {
+    // the counter lives in the row sums, which the last step writes, and B^T
+    // (row-major) where the matrix cores' B would be: one of the two is used
+    ChainGate gate;
+    gate.nnz = at<unsigned long long>(ws, P.o_rowsum);
+    gate.limit = (unsigned long long)(chain_density(P) * (double)P.l * (double)P.m);
+    ThetaArgs th = theta_args(P, c->theta, ws);
+    th.nnz = at<unsigned long long>(ws, P.o_rowsum);
+    IQP_TRY(launch_theta_prep(lc, th), "theta_prep");
+    IQP_TRY(launch_support(lc, support_args(P, c->gens, ws)), "support");
+    IQP_TRY(launch_bitslice(lc, bitslice_ops_args(P, ops, ws)), "bitslice(A)");
+    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32, parity_c_args(P, c->gens, ws)), "parity(C)");
+    IQP_TRY(launch_count(lc, CountArgs{at<uint64_t>(ws, P.o_cbits), P.l_pad, P.mw, th.nnz}),
+            "count(C)");
+    IQP_TRY(launch_bitslice(lc, bitslice_samples_args(P, samples, ws)), "bitslice(Z)");
+    ParityArgs pb = parity_b_args(P, c->gens, ws);
+    pb.gate = gate;
+    pb.when = 1;
+    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32, pb), "parity(B)");
+    pb.R_out = 0;
+    pb.when = 2;
+    IQP_TRY(launch_parity_bs(lc, 3, pb), "parity(B^T, row-major)");
+    FwdArgs fa = fwd_args(P, ws, P.tc.splits);
+    fa.gate = gate;
+    IQP_TRY(launch_phase_fwd(lc, P.prec, P.tc.fm, P.tc.fn, fa), "phase_fwd");
+    EpiArgs ea = epi_args(P, ws, P.tc.splits, phase_out);
+    ea.gate = gate;
+    IQP_TRY(launch_epilogue(lc, ea), "phase_epilogue");
+    IQP_TRY(launch_chain_fwd(lc, ChainFwdArgs{at<uint64_t>(ws, P.o_cbits), P.mw,
+                                              at<float>(ws, P.o_t32), P.m_pad,
+                                              at<uint64_t>(ws, P.o_bbits), P.s_pad / 64, P.l, P.s,
+                                              P.tc.splits, phase_out, at<double>(ws, P.o_part),
+                                              gate}),
+            "chain_fwd");
+    IQP_TRY(launch_finalize(lc, fin_args(P, ws, mean, se, rowsum)), "finalize");
+    return IQP_OK;
+}
+
 static int run_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
                        const uint64_t *samples, void *ws, const LaunchCtx &lc, float *phase_out,
                        double *mean, double *se, double *rowsum) {
@@ -530,6 +588,8 @@ static int run_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
         IQP_TRY(launch_finalize(lc, fin_args(P, ws, mean, se, rowsum)), "finalize");
         return IQP_OK;
     }
+    if (P.prec == IQP_FP32 && (double)P.l * (double)P.s * (double)P.m >= kChainTerms)
+        return run_forward_fp32(P, c, ops, samples, ws, lc, phase_out, mean, se, rowsum);
     IQP_TRY(launch_theta_prep(lc, theta_args(P, c->theta, ws)), "theta_prep");
     IQP_TRY(launch_support(lc, support_args(P, c->gens, ws)), "support");
     IQP_TRY(launch_bitslice(lc, bitslice_ops_args(P, ops, ws)), "bitslice(A)");

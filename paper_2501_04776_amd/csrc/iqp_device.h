@@ -197,6 +197,11 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+// Whether the FP32 forward goes over the non-zero entries of C (ChainGate).
+__device__ __forceinline__ bool chain_on(const ChainGate &g) {
+    return g.nnz && __builtin_amdgcn_readfirstlane((int)(gptr(g.nnz)[0] <= g.limit));
+}
+
 // Sum of one double per thread over a 256-thread block, in a fixed order.
 __device__ __forceinline__ double block_sum_256(double v, double *sh) {
     sh[threadIdx.x] = v;

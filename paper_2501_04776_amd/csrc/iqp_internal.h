@@ -60,6 +60,16 @@ constexpr int64_t kI8MaxSamplesPerUnit = (int64_t)1 << 16;
 // listed; heavier generators are read from their bit rows.
 constexpr int kSupCap = 8;
 
+// The FP32 forward has two ways to the same bits (the FP32 matrix product adds
+// one term at a time, in gate order, and adding a zero term changes nothing):
+// the matrix cores over all gates, or one addition per non-zero entry of C.
+// nnz counts C's entries on the device; at most `limit` of them take the
+// second way. NULL: always the matrix cores.
+struct ChainGate {
+    const unsigned long long *nnz = nullptr;
+    unsigned long long limit = 0;
+};
+
 // ---- per-step arguments -----------------------------------------------------
 // Each step's kernel body takes one of these and a block (or work-unit)
 // index. A single-problem launch passes the struct as the kernel argument; a
@@ -76,6 +86,7 @@ struct ThetaArgs {
     int prec;
     uint16_t *hi, *lo, *mid;
     float *t32;
+    unsigned long long *nnz;  // zeroed when not NULL (ChainGate)
 };
 inline int64_t blocks_of(const ThetaArgs &a) { return ceil_div(a.m_pad, 256); }
 
@@ -118,6 +129,8 @@ struct ParityArgs {
     const uint64_t *Xt;
     int64_t Rw, ldx, R_out, Gw;
     uint64_t *out;
+    ChainGate gate = {};
+    int when = 0;  // 1: only for the matrix cores, 2: only for the other way
 };
 inline int64_t blocks_of(const ParityArgs &a) { return ceil_div(a.Gw * ceil_div(a.Rw, 64), 4); }
 
@@ -129,6 +142,7 @@ struct FwdArgs {
     const float *t32;
     int64_t m_pad, l_pad, s_pad, splits;
     float *E;
+    ChainGate gate = {};  // FP32 only
 };
 inline int64_t fwd_units(const FwdArgs &a, int fm, int fn) {
     return (a.l_pad / (32 * fm)) * ceil_div(a.s_pad / (32 * fn), 4) * a.splits;
@@ -139,7 +153,34 @@ struct EpiArgs {
     int64_t splits, l, s, l_pad, s_pad;
     float *phase_out;
     double *part;
+    ChainGate gate = {};
 };
+
+// Non-zero entries of C (tiled32 bits of l_pad rows, mw gate words) added to *nnz.
+struct CountArgs {
+    const uint64_t *cbits;
+    int64_t l_pad, mw;
+    unsigned long long *nnz;
+};
+constexpr int64_t kCountWords = 2048;  // words per block
+inline int64_t blocks_of(const CountArgs &a) { return ceil_div(a.l_pad * a.mw, kCountWords); }
+
+// The FP32 forward over the non-zero entries of C: cbits tiled32, t32 split by
+// gate parity, btrm B^T row-major (Rw words per gate), the gate words split
+// `splits` ways as the matrix-core kernel splits them.
+struct ChainFwdArgs {
+    const uint64_t *cbits;
+    int64_t mw;
+    const float *t32;
+    int64_t m_pad;
+    const uint64_t *btrm;
+    int64_t Rw, l, s, splits;
+    float *phase_out;
+    double *part;
+    ChainGate gate;
+};
+constexpr int64_t kChainChunk = 2 * kEpiChunk;  // samples per block
+inline int64_t blocks_of(const ChainFwdArgs &a) { return a.l * ceil_div(a.s, kChainChunk); }
 inline int64_t blocks_of(const EpiArgs &a) { return a.l * ceil_div(a.s, kEpiChunk); }
 
 struct FinArgs {
@@ -361,6 +402,8 @@ hipError_t launch_weights(const LaunchCtx &lc, const WeightsArgs &a);
 hipError_t launch_gate_list(const LaunchCtx &lc, const GateListArgs &a);
 hipError_t launch_phase_bwd(const LaunchCtx &lc, int prec, int fm, int fn, const BwdArgs &a);
 hipError_t launch_grad_reduce(const LaunchCtx &lc, const GradArgs &a);
+hipError_t launch_count(const LaunchCtx &lc, const CountArgs &a);
+hipError_t launch_chain_fwd(const LaunchCtx &lc, const ChainFwdArgs &a);
 hipError_t launch_sparse_fwd(const LaunchCtx &lc, const SparseFwdArgs &a);
 hipError_t launch_sparse_bound(const LaunchCtx &lc, const SparseBoundArgs &a);
 hipError_t launch_sparse_bwd(const LaunchCtx &lc, const SparseBwdArgs &a);

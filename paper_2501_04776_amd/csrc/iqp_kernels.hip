@@ -52,6 +52,7 @@ __device__ __forceinline__ uint32_t f32_to_e4m3(float y) {
 // theta_prep
 __device__ __forceinline__ void theta_prep_body(const ThetaArgs &a, int64_t blk) {
     const int64_t i = blk * 256 + threadIdx.x;
+    if (i == 0 && a.nnz) gptr(a.nnz)[0] = 0ull;
     if (i >= a.m_pad) return;
     const double t = i < a.m ? gptr(a.theta)[i] : 0.0;
     const double tr = t - IQP_PI * rint(t * IQP_INV_PI);
@@ -189,6 +190,7 @@ __device__ __forceinline__ void parity_bs_body(const ParityArgs &a, int64_t blk)
     const int lane = threadIdx.x & 63;
     const int64_t unit = blk * 4 + wave_id();
     if (unit >= Gw * ceil_div(Rw, 64)) return;  // uniform over the wave
+    if (a.when && chain_on(a.gate) != (a.when == 2)) return;
     const int64_t rc = unit / Gw, gb = unit - rc * Gw;
     const int64_t rw = rc * 64 + lane;
     const bool live = rw < Rw;
@@ -745,6 +747,7 @@ __device__ __forceinline__ void fwd32_group(const uint64_t (&cw)[FM], const uint
 
 template <int FM, int FN>
 __device__ __forceinline__ void fwd_f32_body(const FwdArgs &a, int64_t gu, int tid) {
+    if (chain_on(a.gate)) return;
     __shared__ float4 lt[2][kChunkWords * 16];
     const uint64_t IQP_GLOBAL *__restrict__ cbits = gptr(a.cbits);
     const uint64_t IQP_GLOBAL *__restrict__ bbits = gptr(a.bbits);
@@ -934,6 +937,7 @@ hipError_t launch_phase_fwd_persistent(const LaunchCtx &lc, int prec, int fm, in
 
 __device__ __forceinline__ void epilogue_body(const EpiArgs &a, int64_t blk) {
     __shared__ double sh[256];
+    if (chain_on(a.gate)) return;
     const float IQP_GLOBAL *__restrict__ E = gptr(a.E);
     float IQP_GLOBAL *__restrict__ phase_out = gptr(a.phase_out);
     double IQP_GLOBAL *__restrict__ part = gptr(a.part);

@@ -113,7 +113,8 @@ inline ThetaArgs theta_args(const Plan &P, const double *theta, void *ws) {
                      at<uint16_t>(ws, P.o_thh),
                      at<uint16_t>(ws, P.o_thl),
                      P.prec == IQP_SPLIT3_BF16 ? at<uint16_t>(ws, P.o_thm) : nullptr,
-                     at<float>(ws, P.o_t32)};
+                     at<float>(ws, P.o_t32),
+                     nullptr};
 }
 inline BitsliceArgs bitslice_ops_args(const Plan &P, const uint64_t *ops, void *ws) {
     return BitsliceArgs{ops, P.l, (int)P.W, P.lda, at<uint64_t>(ws, P.o_xa)};
