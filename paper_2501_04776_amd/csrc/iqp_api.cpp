@@ -207,6 +207,7 @@ static void apply_env_tiles(TileCfg &tc, int prec) {
         ((a == 4 && b == 4) || (a == 2 && b == 4) || (a == 2 && b == 2))) {
         tc.fm = a;
         tc.fn = b;
+        tc.fixed_fwd = true;
     }
     const char *g = getenv("IQP_BWD_TILE");
     if (g && sscanf(g, "%dx%d", &a, &b) == 2 &&
@@ -480,15 +481,11 @@ static SampleParity indep_parity(const Plan &P, const iqp_circuit *c, void *ws) 
 }
 
 // C row-major and the per-observable sample bit columns of the independent
-// estimates.
+// estimates (the support lists are there already).
 static int run_indep_parities(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
                               const uint64_t *samples, void *ws, const LaunchCtx &lc) {
-    IQP_TRY(launch_support(lc, support_args(P, c->gens, ws)), "support");
-    IQP_TRY(launch_bitslice(lc, bitslice_ops_args(P, ops, ws)), "bitslice(A)");
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_ROW_MAJOR,
-                             ParityArgs{c->gens, at<int32_t>(ws, P.o_sup), P.m, (int)P.W,
-                                        at<uint64_t>(ws, P.o_xa), P.l_pad / 64, P.lda, P.l, P.mw,
-                                        at<uint64_t>(ws, P.o_cbits)}),
+    IQP_TRY(launch_parity(lc, IQP_BITS_ROW_MAJOR,
+                          parity_ops_args(P, c->gens, ops, ws, P.l, P.o_cbits)),
             "parity(C, row-major)");
     IQP_TRY(launch_indep_slice(lc, IndepSliceArgs{samples, P.l, P.s, (int)P.W, P.ldz,
                                                   at<uint64_t>(ws, P.o_xz)}),
@@ -499,19 +496,10 @@ static int run_indep_parities(const Plan &P, const iqp_circuit *c, const uint64_
 // Sparse form: the row-major C and B^T parities its kernels walk.
 static int run_sparse_parities(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
                                const uint64_t *samples, void *ws, const LaunchCtx &lc) {
-    IQP_TRY(launch_support(lc, support_args(P, c->gens, ws)), "support");
-    IQP_TRY(launch_bitslice(lc, bitslice_ops_args(P, ops, ws)), "bitslice(A)");
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_ROW_MAJOR,
-                             ParityArgs{c->gens, at<int32_t>(ws, P.o_sup), P.m, (int)P.W,
-                                        at<uint64_t>(ws, P.o_xa), P.l_pad / 64, P.lda, P.l, P.mw,
-                                        at<uint64_t>(ws, P.o_cbits)}),
-            "parity(C, row-major)");
-    IQP_TRY(launch_bitslice(lc, bitslice_samples_args(P, samples, ws)), "bitslice(Z)");
-    IQP_TRY(launch_parity_bs(lc, 3,
-                             ParityArgs{c->gens, at<int32_t>(ws, P.o_sup), P.m, (int)P.W,
-                                        at<uint64_t>(ws, P.o_xz), P.s_pad / 64, P.ldz, 0, P.mw,
-                                        at<uint64_t>(ws, P.o_btbits)}),
-            "parity(B^T, row-major)");
+    IQP_TRY(launch_parity2(lc, IQP_BITS_ROW_MAJOR,
+                           parity_ops_args(P, c->gens, ops, ws, P.l, P.o_cbits), 3,
+                           parity_samples_args(P, c->gens, samples, ws, 0, P.o_btbits)),
+            "parity(C, B^T, row-major)");
     return IQP_OK;
 }
 
@@ -533,6 +521,19 @@ static double chain_density(const Plan &P) {
     return d < 1.0 / 3.0 ? d : 1.0 / 3.0;
 }
 
+// Launches the forward contraction. No element's arithmetic depends on the wave
+// tile, so a product whose 128 x 128 tiles would fill less than half of the
+// wave slots runs in 64 x 64 ones, four times as many waves of a quarter of
+// the length (150 observables, 600 samples, 700 gates, split3-BF16: 38 -> 14
+// us); the splits stay those of the plan's tile.
+static hipError_t launch_fwd(const LaunchCtx &lc, const Plan &P, const FwdArgs &a) {
+    int fm = P.tc.fm, fn = P.tc.fn;
+    if (fm == 4 && fn == 4 &&
+        2 * (P.l_pad / 128) * (P.s_pad / 128) * P.tc.splits <= kWaveSlots && !P.tc.fixed_fwd)
+        fm = fn = 2;
+    return launch_phase_fwd(lc, P.prec, fm, fn, a);
+}
+
 static int run_forward_fp32(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
                             const uint64_t *samples, void *ws, const LaunchCtx &lc,
                             float *phase_out, double *mean, double *se, double *rowsum) {
@@ -543,71 +544,69 @@ static int run_forward_fp32(const Plan &P, const iqp_circuit *c, const uint64_t 
     gate.limit = (unsigned long long)(chain_density(P) * (double)P.l * (double)P.m);
     ThetaArgs th = theta_args(P, c->theta, ws);
     th.nnz = at<unsigned long long>(ws, P.o_rowsum);
-    IQP_TRY(launch_theta_prep(lc, th), "theta_prep");
-    IQP_TRY(launch_support(lc, support_args(P, c->gens, ws)), "support");
-    IQP_TRY(launch_bitslice(lc, bitslice_ops_args(P, ops, ws)), "bitslice(A)");
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32, parity_c_args(P, c->gens, ws)), "parity(C)");
+    IQP_TRY(launch_prep(lc, th, support_args(P, c->gens, ws)), "theta_prep, support");
+    IQP_TRY(launch_parity(lc, IQP_BITS_TILED32, parity_c_args(P, c->gens, ops, ws)), "parity(C)");
     IQP_TRY(launch_count(lc, CountArgs{at<uint64_t>(ws, P.o_cbits), P.l_pad, P.mw, th.nnz}),
             "count(C)");
-    IQP_TRY(launch_bitslice(lc, bitslice_samples_args(P, samples, ws)), "bitslice(Z)");
-    ParityArgs pb = parity_b_args(P, c->gens, ws);
+    ParityArgs pb = parity_b_args(P, c->gens, samples, ws);
     pb.gate = gate;
     pb.when = 1;
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32, pb), "parity(B)");
+    IQP_TRY(launch_parity(lc, IQP_BITS_TILED32, pb), "parity(B)");
     pb.R_out = 0;
     pb.when = 2;
-    IQP_TRY(launch_parity_bs(lc, 3, pb), "parity(B^T, row-major)");
+    IQP_TRY(launch_parity(lc, 3, pb), "parity(B^T, row-major)");
+    const FinArgs fin = fin_args(P, ws, mean, se, rowsum);
     FwdArgs fa = fwd_args(P, ws, P.tc.splits);
     fa.gate = gate;
-    IQP_TRY(launch_phase_fwd(lc, P.prec, P.tc.fm, P.tc.fn, fa), "phase_fwd");
-    EpiArgs ea = epi_args(P, ws, P.tc.splits, phase_out);
+    IQP_TRY(launch_fwd(lc, P, fa), "phase_fwd");
+    EpiArgs ea = epi_args(P, ws, P.tc.splits, phase_out, fin);
     ea.gate = gate;
     IQP_TRY(launch_epilogue(lc, ea), "phase_epilogue");
     IQP_TRY(launch_chain_fwd(lc, ChainFwdArgs{at<uint64_t>(ws, P.o_cbits), P.mw,
                                               at<float>(ws, P.o_t32), P.m_pad,
                                               at<uint64_t>(ws, P.o_bbits), P.s_pad / 64, P.l, P.s,
                                               P.tc.splits, phase_out, at<double>(ws, P.o_part),
-                                              gate}),
+                                              fin, gate}),
             "chain_fwd");
-    IQP_TRY(launch_finalize(lc, fin_args(P, ws, mean, se, rowsum)), "finalize");
+    IQP_TRY(launch_finalize(lc, fin), "finalize");
     return IQP_OK;
 }
 
 static int run_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
                        const uint64_t *samples, void *ws, const LaunchCtx &lc, float *phase_out,
                        double *mean, double *se, double *rowsum) {
+    const FinArgs fin = fin_args(P, ws, mean, se, rowsum);
     if (P.prec == IQP_SPARSE_FP32) {
-        IQP_TRY(launch_theta_prep(lc, theta_args(P, c->theta, ws)), "theta_prep");
+        IQP_TRY(launch_prep(lc, theta_args(P, c->theta, ws), support_args(P, c->gens, ws)),
+                "theta_prep, support");
         int st = run_sparse_parities(P, c, ops, samples, ws, lc);
         if (st) return st;
         IQP_TRY(launch_sparse_fwd(lc, SparseFwdArgs{at<uint64_t>(ws, P.o_cbits), P.mw,
                                                     at<float>(ws, P.o_t32), shared_parity(P, ws),
                                                     P.l, P.s, phase_out,
-                                                    at<double>(ws, P.o_part)}),
+                                                    at<double>(ws, P.o_part), fin}),
                 "sparse_fwd");
-        IQP_TRY(launch_finalize(lc, fin_args(P, ws, mean, se, rowsum)), "finalize");
+        IQP_TRY(launch_finalize(lc, fin), "finalize");
         return IQP_OK;
     }
     if (P.prec == IQP_FP32 && (double)P.l * (double)P.s * (double)P.m >= kChainTerms)
         return run_forward_fp32(P, c, ops, samples, ws, lc, phase_out, mean, se, rowsum);
-    IQP_TRY(launch_theta_prep(lc, theta_args(P, c->theta, ws)), "theta_prep");
-    IQP_TRY(launch_support(lc, support_args(P, c->gens, ws)), "support");
-    IQP_TRY(launch_bitslice(lc, bitslice_ops_args(P, ops, ws)), "bitslice(A)");
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32, parity_c_args(P, c->gens, ws)), "parity(C)");
-    IQP_TRY(launch_bitslice(lc, bitslice_samples_args(P, samples, ws)), "bitslice(Z)");
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32, parity_b_args(P, c->gens, ws)), "parity(B)");
-    IQP_TRY(launch_phase_fwd(lc, P.prec, P.tc.fm, P.tc.fn, fwd_args(P, ws, P.tc.splits)),
-            "phase_fwd");
-    IQP_TRY(launch_epilogue(lc, epi_args(P, ws, P.tc.splits, phase_out)), "phase_epilogue");
-    IQP_TRY(launch_finalize(lc, fin_args(P, ws, mean, se, rowsum)), "finalize");
+    IQP_TRY(launch_prep(lc, theta_args(P, c->theta, ws), support_args(P, c->gens, ws)),
+            "theta_prep, support");
+    IQP_TRY(launch_parity2(lc, IQP_BITS_TILED32, parity_c_args(P, c->gens, ops, ws),
+                           IQP_BITS_TILED32, parity_b_args(P, c->gens, samples, ws)),
+            "parity(C, B)");
+    IQP_TRY(launch_fwd(lc, P, fwd_args(P, ws, P.tc.splits)), "phase_fwd");
+    IQP_TRY(launch_epilogue(lc, epi_args(P, ws, P.tc.splits, phase_out, fin)), "phase_epilogue");
+    IQP_TRY(launch_finalize(lc, fin), "finalize");
     return IQP_OK;
 }
 
-// Backward from the coefficients at o_coef and the phases `phase`. When the
-// forward ran in the same call, the bit columns of A and Z are already in the
-// workspace.
+// Backward from the coefficients at o_coef and the phases `phase`. The support
+// lists are there already, and after a sparse forward in the same call (`same`)
+// its parities too.
 static int run_backward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
-                        const uint64_t *samples, const float *phase, bool bitcols_ready, void *ws,
+                        const uint64_t *samples, const float *phase, bool same, void *ws,
                         const LaunchCtx &lc, double *grad_theta) {
     if (P.prec == IQP_SPARSE_FP32) {
         long long *acc = at<long long>(ws, P.o_acc);
@@ -615,7 +614,7 @@ static int run_backward(const Plan &P, const iqp_circuit *c, const uint64_t *ops
         IQP_TRY(launch_sparse_bound(lc, SparseBoundArgs{at<double>(ws, P.o_coef), P.l, P.s,
                                                         P.m_pad, acc, scale}),
                 "sparse_bound");
-        if (!bitcols_ready) {
+        if (!same) {
             int st = run_sparse_parities(P, c, ops, samples, ws, lc);
             if (st) return st;
         }
@@ -628,15 +627,9 @@ static int run_backward(const Plan &P, const iqp_circuit *c, const uint64_t *ops
         return IQP_OK;
     }
     IQP_TRY(launch_weights(lc, weights_args(P, phase, ws)), "weights");
-    if (!bitcols_ready) {
-        IQP_TRY(launch_support(lc, support_args(P, c->gens, ws)), "support");
-        IQP_TRY(launch_bitslice(lc, bitslice_ops_args(P, ops, ws)), "bitslice(A)");
-        IQP_TRY(launch_bitslice(lc, bitslice_samples_args(P, samples, ws)), "bitslice(Z)");
-    }
-    IQP_TRY(launch_parity_bs(lc, kBitsWordMajor, parity_bt_args(P, c->gens, ws)),
-            "parity(B^T)");
-    IQP_TRY(launch_parity_bs(lc, kBitsWordMajor, parity_ct_args(P, c->gens, ws)),
-            "parity(C^T)");
+    IQP_TRY(launch_parity2(lc, kBitsWordMajor, parity_bt_args(P, c->gens, samples, ws),
+                           kBitsWordMajor, parity_ct_args(P, c->gens, ops, ws)),
+            "parity(B^T, C^T)");
     IQP_TRY(launch_gate_list(lc, gate_list_args(P, ws, P.tc.bfm, P.tc.bfn)), "gate_list");
     IQP_TRY(launch_phase_bwd(lc, P.prec, P.tc.bfm, P.tc.bfn, bwd_args(P, ws)), "phase_bwd");
     IQP_TRY(launch_grad_reduce(lc, grad_args(P, ws, P.tc.bfm, grad_theta)), "grad_reduce");
@@ -745,18 +738,13 @@ int iqp_parity(int64_t n_rows, const uint64_t *rows, int64_t n_cols, const uint6
     uint64_t *xt = static_cast<uint64_t *>(ws);
     int32_t *sup = at<int32_t>(ws, parity_xt_bytes(n_rows, n_words, layout));
     const int64_t Gw = ceil_div(n_cols, 64);
-    IQP_TRY(launch_bitslice(lc, BitsliceArgs{rows, n_rows, n_words, ldx, xt}), "bitslice");
     IQP_TRY(launch_support(lc, SupportArgs{cols, n_cols, n_words, Gw * 64, sup}), "support");
-    if (layout == IQP_BITS_TILED32_T)
-        IQP_TRY(launch_parity_bs(lc, layout,
-                                 ParityArgs{cols, sup, n_cols, n_words, xt, ceil_div(n_rows, 64),
-                                            ldx, 0, Gw, out}),
-                "parity");
-    else
-        IQP_TRY(launch_parity_bs(lc, layout,
-                                 ParityArgs{cols, sup, n_cols, n_words, xt, rw, ldx, R_out, Gw,
-                                            out}),
-                "parity");
+    const bool transposed = layout == IQP_BITS_TILED32_T;
+    IQP_TRY(launch_parity(lc, layout,
+                          parity_args(rows, n_rows, cols, sup, n_cols, n_words, xt, ldx,
+                                      transposed ? ceil_div(n_rows, 64) : rw,
+                                      transposed ? 0 : R_out, Gw, out)),
+            "parity");
     return IQP_OK;
 }
 
@@ -790,7 +778,9 @@ int iqp_expval_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops, int64_
         if (st) return st;
         phase = at<float>(ws, P.o_phi);
     }
-    IQP_TRY(launch_coef_plain(lc, coef_args(P, grad_mean, ws)), "coef");
+    // (the support lists again after a forward in this call: one launch anyway)
+    IQP_TRY(launch_prep(lc, coef_args(P, grad_mean, ws), support_args(P, c->gens, ws)),
+            "coef, support");
     return run_backward(P, c, ops, samples, phase, phase_save == nullptr, ws, lc, grad_theta);
 }
 
@@ -798,15 +788,17 @@ int iqp_expval_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops, int64_
 static int run_indep_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
                              const uint64_t *samples, void *ws, const LaunchCtx &lc,
                              float *phase_out, double *mean, double *se) {
-    IQP_TRY(launch_theta_prep(lc, theta_args(P, c->theta, ws)), "theta_prep");
+    IQP_TRY(launch_prep(lc, theta_args(P, c->theta, ws), support_args(P, c->gens, ws)),
+            "theta_prep, support");
     int st = run_indep_parities(P, c, ops, samples, ws, lc);
     if (st) return st;
+    const FinArgs fin = fin_args(P, ws, mean, se, at<double>(ws, P.o_rowsum));
     IQP_TRY(launch_sparse_fwd(lc, SparseFwdArgs{at<uint64_t>(ws, P.o_cbits), P.mw,
                                                 at<float>(ws, P.o_t32), indep_parity(P, c, ws),
-                                                P.l, P.s, phase_out, at<double>(ws, P.o_part)}),
+                                                P.l, P.s, phase_out, at<double>(ws, P.o_part),
+                                                fin}),
             "sparse_fwd(indep)");
-    IQP_TRY(launch_finalize(lc, fin_args(P, ws, mean, se, at<double>(ws, P.o_rowsum))),
-            "finalize");
+    IQP_TRY(launch_finalize(lc, fin), "finalize");
     return IQP_OK;
 }
 
@@ -855,10 +847,10 @@ int iqp_expval_indep_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops, 
                                     nullptr)))
             return st;
         phase = at<float>(ws, P.o_phi);
-    } else if ((st = run_indep_parities(P, c, ops, samples, ws, lc))) {
-        return st;
     }
-    IQP_TRY(launch_coef_plain(lc, coef_args(P, grad_mean, ws)), "coef");
+    IQP_TRY(launch_prep(lc, coef_args(P, grad_mean, ws), support_args(P, c->gens, ws)),
+            "coef, support");
+    if (phase_save && (st = run_indep_parities(P, c, ops, samples, ws, lc))) return st;
     long long *acc = at<long long>(ws, P.o_acc);
     double *scale = at<double>(ws, P.o_scale);
     IQP_TRY(launch_sparse_bound(lc, SparseBoundArgs{at<double>(ws, P.o_coef), P.l, P.s, P.m_pad,
@@ -911,17 +903,17 @@ int iqp_mmd_loss_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops,
 // Forward of a bitflip circuit into the plan's buffers (mean may be the
 // workspace's own slot).
 static int run_bitflip_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
-                               void *ws, const LaunchCtx &lc, double *mean) {
-    IQP_TRY(launch_bitflip_prep(lc, BitflipPrepArgs{c->theta, P.m, at<double>(ws, P.o_enc)}),
-            "bitflip_prep");
-    IQP_TRY(launch_support(lc, support_args(P, c->gens, ws)), "support");
-    IQP_TRY(launch_bitslice(lc, BitsliceArgs{ops, P.l, (int)P.W, P.lda, at<uint64_t>(ws, P.o_xa)}),
-            "bitslice(A)");
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32,
-                             ParityArgs{c->gens, at<int32_t>(ws, P.o_sup), P.m, (int)P.W,
-                                        at<uint64_t>(ws, P.o_xa), P.l_pad / 64, P.lda, P.l_pad,
-                                        P.mw, at<uint64_t>(ws, P.o_cbits)}),
-            "parity(C)");
+                               void *ws, const LaunchCtx &lc, double *mean, bool grad) {
+    IQP_TRY(launch_prep(lc, BitflipPrepArgs{c->theta, P.m, at<double>(ws, P.o_enc)},
+                        support_args(P, c->gens, ws)),
+            "bitflip_prep, support");
+    const ParityArgs pc = parity_ops_args(P, c->gens, ops, ws, P.l_pad, P.o_cbits);
+    if (grad)
+        IQP_TRY(launch_parity2(lc, IQP_BITS_TILED32, pc, IQP_BITS_TILED32_T,
+                               parity_ops_args(P, c->gens, ops, ws, 0, P.o_ctbits)),
+                "parity(C, C^T)");
+    else
+        IQP_TRY(launch_parity(lc, IQP_BITS_TILED32, pc), "parity(C)");
     IQP_TRY(launch_bitflip_fwd(lc, BitflipFwdArgs{at<uint64_t>(ws, P.o_cbits),
                                                    at<double>(ws, P.o_enc), P.l, P.mw, mean,
                                                    nullptr, at<double>(ws, P.o_stat)}),
@@ -941,7 +933,7 @@ int iqp_bitflip_expval(const iqp_circuit *c, int64_t l, const uint64_t *ops, dou
     make_bitflip_plan(P, false, c->n_qubits, c->n_gates, l);
     if ((st = check_ws(P, ws, ws_bytes))) return st;
     if ((st = check_device())) return st;
-    return run_bitflip_forward(P, c, ops, ws, make_ctx(stream), mean);
+    return run_bitflip_forward(P, c, ops, ws, make_ctx(stream), mean, false);
 }
 
 int iqp_bitflip_expval_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops,
@@ -959,13 +951,8 @@ int iqp_bitflip_expval_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops
     if ((st = check_ws(P, ws, ws_bytes))) return st;
     if ((st = check_device())) return st;
     LaunchCtx lc = make_ctx(stream);
-    st = run_bitflip_forward(P, c, ops, ws, lc, at<double>(ws, P.o_rowsum));
+    st = run_bitflip_forward(P, c, ops, ws, lc, at<double>(ws, P.o_rowsum), true);
     if (st) return st;
-    IQP_TRY(launch_parity_bs(lc, IQP_BITS_TILED32_T,
-                             ParityArgs{c->gens, at<int32_t>(ws, P.o_sup), P.m, (int)P.W,
-                                        at<uint64_t>(ws, P.o_xa), P.lw, P.lda, 0, P.mw,
-                                        at<uint64_t>(ws, P.o_ctbits)}),
-            "parity(C^T)");
     IQP_TRY(launch_bitflip_grad(lc, BitflipGradArgs{at<uint64_t>(ws, P.o_ctbits),
                                                      at<double>(ws, P.o_enc), c->theta,
                                                      at<double>(ws, P.o_stat), grad_mean, P.m,

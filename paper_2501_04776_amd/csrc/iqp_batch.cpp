@@ -54,6 +54,7 @@ struct StepRec {
     size_t args_off, off_off;  // byte offsets in the table
     int jobs;
     int64_t total;  // blocks (batched) or work units (persistent)
+    size_t lds;     // dynamic LDS bytes
 };
 
 // Host image of a pass's argument table; arrays 64-byte aligned.
@@ -67,7 +68,8 @@ struct Table {
         return o;
     }
     template <typename A>
-    void add(int kind, const std::vector<A> &args, const std::vector<int64_t> &counts) {
+    void add(int kind, const std::vector<A> &args, const std::vector<int64_t> &counts,
+             size_t lds = 0) {
         std::vector<int64_t> off(args.size() + 1, 0);
         for (size_t i = 0; i < args.size(); ++i) off[i + 1] = off[i] + counts[i];
         StepRec r;
@@ -76,6 +78,7 @@ struct Table {
         r.off_off = push(off.data(), sizeof(int64_t) * off.size());
         r.jobs = (int)args.size();
         r.total = off.back();
+        r.lds = lds;
         steps.push_back(r);
     }
 };
@@ -223,17 +226,27 @@ static void build_table(const iqp_batch_plan *bp, int pass, const iqp_problem *p
         const iqp_problem *q = pr(p);
         su.push_back(support_args(P, q ? q->circuit.gens : nullptr, base(p)));
         sun.push_back(blocks_of(su.back()));
-        bs.push_back(bitslice_ops_args(P, q ? q->ops : nullptr, base(p)));
-        bs.push_back(bitslice_samples_args(P, q ? q->samples : nullptr, base(p)));
         const uint64_t *g = q ? q->circuit.gens : nullptr;
+        const uint64_t *ops = q ? q->ops : nullptr, *z = q ? q->samples : nullptr;
         if (pass == 0) {
-            par.push_back(parity_c_args(P, g, base(p)));
-            par.push_back(parity_b_args(P, g, base(p)));
+            par.push_back(parity_c_args(P, g, ops, base(p)));
+            par.push_back(parity_b_args(P, g, z, base(p)));
         } else {
-            par.push_back(parity_bt_args(P, g, base(p)));
-            par.push_back(parity_ct_args(P, g, base(p)));
+            par.push_back(parity_bt_args(P, g, z, base(p)));
+            par.push_back(parity_ct_args(P, g, ops, base(p)));
         }
     }
+    // rows of many words: bit columns, and the parities that gather them
+    size_t lds = 0;
+    std::vector<ParityArgs> rowpar, colpar;
+    for (auto &a : par) {
+        if (!a.rw) bs.push_back(columns_of(a));
+        (a.rw ? rowpar : colpar).push_back(a);
+        lds = std::max(lds, lds_of(a));
+    }
+    std::vector<int64_t> colparn;
+    for (auto &a : colpar) colparn.push_back(blocks_of(a));
+    par.swap(rowpar);
     for (auto &a : bs) bsn.push_back(blocks_of(a));
     for (auto &a : par) parn.push_back(blocks_of(a));
 
@@ -252,9 +265,9 @@ static void build_table(const iqp_batch_plan *bp, int pass, const iqp_problem *p
             const Plan &P = bp->plans[p];
             const iqp_problem *q = pr(p);
             th.push_back(theta_args(P, q ? q->circuit.theta : nullptr, base(p)));
-            ep.push_back(epi_args(P, base(p), sp[p], q ? q->phase_save : nullptr));
             fi.push_back(fin_args(P, base(p), q ? q->mean : nullptr, q ? q->stderr_ : nullptr,
                                   nullptr));
+            ep.push_back(epi_args(P, base(p), sp[p], q ? q->phase_save : nullptr, fi.back()));
             thn.push_back(blocks_of(th.back()));
             epn.push_back(blocks_of(ep.back()));
             fin.push_back(blocks_of(fi.back()));
@@ -271,7 +284,8 @@ static void build_table(const iqp_batch_plan *bp, int pass, const iqp_problem *p
         tb.add(SK_THETA, th, thn);
         tb.add(SK_SUPPORT, su, sun);
         tb.add(SK_BITSLICE, bs, bsn);
-        tb.add(SK_PARITY1, par, parn);
+        tb.add(SK_PARITY1, par, parn, lds);
+        tb.add(SK_COLPARITY1, colpar, colparn);
         tb.add(SK_FWD_PERSISTENT, fw, fwn);
         tb.add(SK_EPI, ep, epn);
         tb.add(SK_FIN, fi, fin);
@@ -306,7 +320,8 @@ static void build_table(const iqp_batch_plan *bp, int pass, const iqp_problem *p
         tb.add(SK_WEIGHTS, we, wen);
         tb.add(SK_SUPPORT, su, sun);
         tb.add(SK_BITSLICE, bs, bsn);
-        tb.add(SK_PARITY4, par, parn);
+        tb.add(SK_PARITY4, par, parn, lds);
+        tb.add(SK_COLPARITY4, colpar, colparn);
         tb.add(SK_GATELIST, gl, gln);
         tb.add(SK_BWD_PERSISTENT, bw, bwn);
         tb.add(SK_GRAD, gr, grn);
@@ -339,7 +354,7 @@ static int enqueue_pass(const iqp_batch_plan *bp, int pass, const Table &tb, voi
                                                 counter, grid),
                     "phase_bwd (persistent)");
         } else {
-            IQP_TRY(launch_batched(lc, r.kind, args, off, r.jobs, r.total), "batched step");
+            IQP_TRY(launch_batched(lc, r.kind, args, off, r.jobs, r.total, r.lds), "batched step");
         }
     }
     return IQP_OK;

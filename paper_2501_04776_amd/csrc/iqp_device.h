@@ -98,12 +98,37 @@ __global__ __launch_bounds__(256) void batched_kernel(const A *__restrict__ args
 constexpr int64_t kMaxBlocks = ((int64_t)1 << 24) - 1;
 
 template <typename A, void (*F)(const A &, int64_t)>
-static hipError_t plain_launch(const LaunchCtx &lc, int family, const A &a, int64_t blocks) {
+static hipError_t plain_launch(const LaunchCtx &lc, int family, const A &a, int64_t blocks,
+                               size_t lds = 0) {
     if (blocks <= 0) return hipSuccess;
     if (blocks > kMaxBlocks) return hipErrorInvalidConfiguration;
     hipEvent_t ev;
     timed_begin(lc, family, &ev);
-    hipLaunchKernelGGL((plain_kernel<A, F>), dim3((unsigned)blocks), dim3(256), 0, lc.stream, a);
+    hipLaunchKernelGGL((plain_kernel<A, F>), dim3((unsigned)blocks), dim3(256), lds, lc.stream, a);
+    hipError_t e = hipGetLastError();
+    timed_end(lc, family, ev);
+    return e;
+}
+
+// Two independent steps in one launch: blocks 0 .. na - 1 run F on a, the
+// others G on b.
+template <typename A, void (*F)(const A &, int64_t), typename B, void (*G)(const B &, int64_t)>
+__global__ __launch_bounds__(256) void pair_kernel(A a, B b, int64_t na) {
+    if ((int64_t)blockIdx.x < na) F(a, (int64_t)blockIdx.x);
+    else G(b, (int64_t)blockIdx.x - na);
+}
+
+template <typename A, void (*F)(const A &, int64_t), typename B, void (*G)(const B &, int64_t)>
+static hipError_t pair_launch(const LaunchCtx &lc, int family, const A &a, int64_t na, const B &b,
+                              int64_t nb, size_t lds = 0) {
+    if (na + nb > kMaxBlocks) {  // past one grid
+        const hipError_t e = plain_launch<A, F>(lc, family, a, na, lds);
+        return e != hipSuccess ? e : plain_launch<B, G>(lc, family, b, nb, lds);
+    }
+    hipEvent_t ev;
+    timed_begin(lc, family, &ev);
+    hipLaunchKernelGGL((pair_kernel<A, F, B, G>), dim3((unsigned)(na + nb)), dim3(256), lds,
+                       lc.stream, a, b, na);
     hipError_t e = hipGetLastError();
     timed_end(lc, family, ev);
     return e;
@@ -195,6 +220,19 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
     small_stage<2, 1, 0x33333333u>(lo, hi, lane);
     small_stage<1, 0, 0x55555555u>(lo, hi, lane);
     return ((uint64_t)hi << 32) | lo;
+}
+
+// Mean and standard error of observable k from its sums of cos and cos^2.
+__device__ __forceinline__ void finalize_store(const FinArgs &a, int64_t k, double sc, double sc2) {
+    const double S = (double)a.s;
+    const double mu = sc / S;
+    const double var = sc2 / S - mu * mu;
+    if (a.mean) gptr(a.mean)[k] = mu;
+    if (a.stderr_) gptr(a.stderr_)[k] = sqrt((var > 0.0 ? var : 0.0) / S);
+    if (a.rowsum) {
+        gptr(a.rowsum)[2 * k + 0] = sc;
+        gptr(a.rowsum)[2 * k + 1] = sc2;
+    }
 }
 
 // Whether the FP32 forward goes over the non-zero entries of C (ChainGate).

@@ -26,6 +26,7 @@ __host__ __device__ inline int64_t round_up(int64_t a, int64_t b) { return ceil_
 // Tile configuration of the two contractions (wave tile = 32*fm x 32*fn).
 struct TileCfg {
     int fm = 4, fn = 4;      // forward: observables x samples
+    bool fixed_fwd = false;  // the forward tile was asked for
     int bfm = 2, bfn = 2;    // backward: observables x gates
     int64_t splits = 0;      // forward split over gate words; 0 = choose
     int64_t bsplits = 0;     // backward split over sample words; 0 = choose
@@ -115,24 +116,60 @@ struct SupportArgs {
 inline int64_t blocks_of(const SupportArgs &a) { return ceil_div(a.rows, 256); }
 
 // Parity of each generator (m of them, W words each, support lists `sup`
-// covering 64 Gw rows) against the rows behind Xt (Rw words of 64 rows), in
-// layout 0 (row-major), 1 (tiled32), 2 (transposed tiled32), 3 (transposed
-// row-major) or 4 (transposed word-major); Gw = output words per row in
-// layouts 0/1, generator words in the others. One wave per 64
-// generators x 64 row words.
+// covering 64 Gw rows) against `rows` (R of them, those past R read as 0; Rw
+// words of 64 rows), in layout 0 (row-major), 1 (tiled32), 2 (transposed
+// tiled32), 3 (transposed row-major) or 4 (transposed word-major); Gw = output
+// words per row in layouts 0/1, generator words in the others.
+// A block of the kernel takes rw row words and 64 gpb generators; from
+// kColumnWords words per row on, rw is 0 and the kernel reads the bit columns
+// Xt (ldx words each) that launch_parity makes first.
 constexpr int kBitsWordMajor = 4;
+constexpr int kColumnWords = 128;
 struct ParityArgs {
+    const uint64_t *rows;
+    int64_t R;
     const uint64_t *gens;
     const int32_t *sup;
     int64_t m;
     int W;
-    const uint64_t *Xt;
-    int64_t Rw, ldx, R_out, Gw;
+    uint64_t *Xt;
+    int64_t ldx;
+    int64_t Rw, R_out, Gw;
     uint64_t *out;
+    int rw;
+    int64_t gpb;
     ChainGate gate = {};
     int when = 0;  // 1: only for the matrix cores, 2: only for the other way
 };
-inline int64_t blocks_of(const ParityArgs &a) { return ceil_div(a.Gw * ceil_div(a.Rw, 64), 4); }
+// Row words per block, the most that leave room for two blocks in a CU's LDS,
+// and the stride of a qubit's words there: an odd stride (or one of 1 or 2)
+// spreads the gathers over the banks.
+inline int parity_rw(int W) {
+    return W <= 7 ? 16 : W <= 17 ? 8 : W <= 31 ? 4 : W <= 63 ? 2 : W < kColumnWords ? 1 : 0;
+}
+__host__ __device__ constexpr int parity_stride(int rw) { return rw >= 4 ? rw + 1 : rw; }
+// Generators per block so that about three blocks run per CU: the transposes
+// that stage a block's rows are paid once for all of them.
+inline ParityArgs parity_args(const uint64_t *rows, int64_t R, const uint64_t *gens,
+                              const int32_t *sup, int64_t m, int W, uint64_t *Xt, int64_t ldx,
+                              int64_t Rw, int64_t R_out, int64_t Gw, uint64_t *out) {
+    ParityArgs a{rows, R, gens, sup, m, W, Xt, ldx, Rw, R_out, Gw, out, parity_rw(W), 4};
+    if (a.rw) {
+        const int64_t want = ceil_div(Gw * ceil_div(Rw, a.rw), 768);
+        a.gpb = want < 4 ? 4 : want > 64 ? 64 : round_up(want, 4);
+    }
+    return a;
+}
+inline int64_t blocks_of(const ParityArgs &a) {
+    return a.rw ? ceil_div(a.Rw, a.rw) * ceil_div(a.Gw, a.gpb)
+                : ceil_div(a.Gw * ceil_div(a.Rw, 64), 4);
+}
+inline size_t lds_of(const ParityArgs &a) {
+    return a.rw ? (size_t)(64 * a.W + 1) * parity_stride(a.rw) * 8 : 0;
+}
+inline BitsliceArgs columns_of(const ParityArgs &a) {
+    return BitsliceArgs{a.rows, a.R, a.W, a.ldx, a.Xt};
+}
 
 // E = C Theta B^T, tiled over observables x samples, gate words split
 // `splits` ways (partials E[split][l_pad][s_pad]).
@@ -148,11 +185,20 @@ inline int64_t fwd_units(const FwdArgs &a, int fm, int fn) {
     return (a.l_pad / (32 * fm)) * ceil_div(a.s_pad / (32 * fn), 4) * a.splits;
 }
 
+// With one chunk per observable (s <= kEpiChunk) the kernel that has the sums
+// writes the results itself.
+struct FinArgs {
+    const double *part;
+    int64_t l, s;
+    double *mean, *stderr_, *rowsum;
+};
+
 struct EpiArgs {
     const float *E;
     int64_t splits, l, s, l_pad, s_pad;
     float *phase_out;
     double *part;
+    FinArgs fin = {};
     ChainGate gate = {};
 };
 
@@ -177,18 +223,16 @@ struct ChainFwdArgs {
     int64_t Rw, l, s, splits;
     float *phase_out;
     double *part;
+    FinArgs fin;
     ChainGate gate;
 };
 constexpr int64_t kChainChunk = 2 * kEpiChunk;  // samples per block
 inline int64_t blocks_of(const ChainFwdArgs &a) { return a.l * ceil_div(a.s, kChainChunk); }
 inline int64_t blocks_of(const EpiArgs &a) { return a.l * ceil_div(a.s, kEpiChunk); }
 
-struct FinArgs {
-    const double *part;
-    int64_t l, s;
-    double *mean, *stderr_, *rowsum;
-};
-inline int64_t blocks_of(const FinArgs &a) { return ceil_div(a.l, 256); }
+inline int64_t blocks_of(const FinArgs &a) {
+    return a.s <= kEpiChunk ? 0 : ceil_div(a.l, 256);
+}
 
 // coef[2k], coef[2k+1] = alpha_k, beta_k of the backward weights. For the
 // fixed-point weights (IQP_SPLIT3_BF16) also the row scale
@@ -345,6 +389,7 @@ struct SparseFwdArgs {
     int64_t l, s;
     float *phase_out;  // [l][s] or NULL
     double *part;      // [l][ceil(s / kEpiChunk)][2] as the dense epilogue writes it
+    FinArgs fin;
 };
 
 // acc[m_pad + 1] int64 (the last slot flags a non-finite contribution) and
@@ -390,10 +435,15 @@ inline int64_t blocks_of(const SparseFinishArgs &a) { return ceil_div(a.m, 256);
 
 // ---- launchers (iqp_kernels.hip, iqp_sparse_kernels.hip); each returns
 // hipGetLastError() ----
-hipError_t launch_theta_prep(const LaunchCtx &lc, const ThetaArgs &a);
-hipError_t launch_bitslice(const LaunchCtx &lc, const BitsliceArgs &a);
+hipError_t launch_prep(const LaunchCtx &lc, const ThetaArgs &a, const SupportArgs &b);
+hipError_t launch_prep(const LaunchCtx &lc, const CoefArgs &a, const SupportArgs &b);
+hipError_t launch_prep(const LaunchCtx &lc, const BitflipPrepArgs &a, const SupportArgs &b);
 hipError_t launch_support(const LaunchCtx &lc, const SupportArgs &a);
-hipError_t launch_parity_bs(const LaunchCtx &lc, int layout, const ParityArgs &a);
+// Parities in one layout, or of two row sets: (la, lb) one of (1, 1), (4, 4),
+// (0, 3), (1, 2).
+hipError_t launch_parity(const LaunchCtx &lc, int layout, const ParityArgs &a);
+hipError_t launch_parity2(const LaunchCtx &lc, int la, const ParityArgs &a, int lb,
+                          const ParityArgs &b);
 hipError_t launch_phase_fwd(const LaunchCtx &lc, int prec, int fm, int fn, const FwdArgs &a);
 hipError_t launch_epilogue(const LaunchCtx &lc, const EpiArgs &a);
 hipError_t launch_finalize(const LaunchCtx &lc, const FinArgs &a);
@@ -409,7 +459,6 @@ hipError_t launch_sparse_bound(const LaunchCtx &lc, const SparseBoundArgs &a);
 hipError_t launch_sparse_bwd(const LaunchCtx &lc, const SparseBwdArgs &a);
 hipError_t launch_sparse_finish(const LaunchCtx &lc, const SparseFinishArgs &a);
 hipError_t launch_indep_slice(const LaunchCtx &lc, const IndepSliceArgs &a);
-hipError_t launch_bitflip_prep(const LaunchCtx &lc, const BitflipPrepArgs &a);
 hipError_t launch_bitflip_fwd(const LaunchCtx &lc, const BitflipFwdArgs &a);
 hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a);
 
@@ -417,11 +466,11 @@ hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a);
 // step's type and `off` a device array of np + 1 prefix sums of their block
 // counts (off[0] = 0, off[np] = total > 0).
 enum StepKind {
-    SK_THETA = 0, SK_BITSLICE, SK_PARITY0, SK_PARITY1, SK_PARITY4, SK_EPI, SK_FIN, SK_COEF,
-    SK_WEIGHTS, SK_GRAD, SK_SUPPORT, SK_GATELIST, SK_COUNT
+    SK_THETA = 0, SK_BITSLICE, SK_PARITY1, SK_PARITY4, SK_EPI, SK_FIN, SK_COEF,
+    SK_WEIGHTS, SK_GRAD, SK_SUPPORT, SK_GATELIST, SK_COLPARITY1, SK_COLPARITY4, SK_COUNT
 };
 hipError_t launch_batched(const LaunchCtx &lc, int kind, const void *args, const int64_t *off,
-                          int np, int64_t total);
+                          int np, int64_t total, size_t lds);
 
 // Persistent contractions over a work queue: `grid` workgroups take work
 // units 0 .. off[np]-1 in order from `counter` (which must read 0 at launch);

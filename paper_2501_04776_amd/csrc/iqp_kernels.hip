@@ -3,9 +3,10 @@
 //   theta_prep      theta -> 2 theta' (theta' = theta reduced to [-pi/2, pi/2]
 //                   by whole multiples of pi), as FP32 or two / three BF16
 //                   limbs
-//   bitslice,       bit-exact popcount(row AND col) mod 2 matrices (the
-//   parity_bs       exponents of B and C, Sec. 2.2) as XORs of per-qubit bit
-//                   columns, with in-register 64x64 bit transposes
+//   parity          bit-exact popcount(row AND col) mod 2 matrices (the
+//                   exponents of B and C, Sec. 2.2) as XORs of per-qubit bit
+//                   columns, staged in LDS by 64x64 bit transposes (bitslice,
+//                   parity_bs: through memory, for rows of 128 words and more)
 //   phase_fwd       E = C Theta B^T (eq. Emat) on the matrix cores, operands
 //                   expanded from parity bits in registers
 //   epilogue        FP64 reduction of E modulo 2 pi, cos, per-chunk sums of
@@ -86,10 +87,6 @@ __device__ __forceinline__ void theta_prep_body(const ThetaArgs &a, int64_t blk)
     }
 }
 
-hipError_t launch_theta_prep(const LaunchCtx &lc, const ThetaArgs &a) {
-    return plain_launch<ThetaArgs, theta_prep_body>(lc, KF_THETA, a, blocks_of(a));
-}
-
 // ---------------------------------------------------------------------------
 // Parity bits, bit-sliced. parity(x, g) = XOR over the qubits q of g of x_q,
 // so with the rows transposed into per-qubit bit columns Xt[q] (bit r = qubit
@@ -122,14 +119,22 @@ __device__ __forceinline__ void support_body(const SupportArgs &a, int64_t blk) 
     for (int k = 0; k < kSupCap; ++k) s[k] = -1;
     int cnt = 0;
     if (j < a.m) {
-        for (int w = 0; w < a.W; ++w) {
-            uint64_t x = gptr(a.gens)[j * a.W + w];
-            while (x) {
-                const int32_t q = w * 64 + __builtin_ctzll(x);
-                x &= x - 1;
+        // eight words in flight: the row's loads, not the bits, take the time
+        for (int w0 = 0; w0 < a.W; w0 += 8) {
+            uint64_t xs[8];
 #pragma unroll
-                for (int k = 0; k < kSupCap; ++k) s[k] = (cnt == k) ? q : s[k];
-                ++cnt;
+            for (int i = 0; i < 8; ++i)
+                xs[i] = w0 + i < a.W ? gptr(a.gens)[j * a.W + w0 + i] : 0ull;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                uint64_t x = xs[i];
+                while (x) {
+                    const int32_t q = (w0 + i) * 64 + __builtin_ctzll(x);
+                    x &= x - 1;
+#pragma unroll
+                    for (int k = 0; k < kSupCap; ++k) s[k] = (cnt == k) ? q : s[k];
+                    ++cnt;
+                }
             }
         }
     }
@@ -273,22 +278,215 @@ __device__ __forceinline__ void parity_bs_body(const ParityArgs &a, int64_t blk)
     }
 }
 
-hipError_t launch_bitslice(const LaunchCtx &lc, const BitsliceArgs &a) {
-    return plain_launch<BitsliceArgs, bitslice_body>(lc, KF_PARITY, a, blocks_of(a));
+// Parities straight from the rows. A block stages rw row words of every qubit
+// in LDS, Xs[q * st + i] = bit column q of row word i, by transposing the 64x64
+// blocks of its rows (a wave per block), a zero column last; then a lane takes
+// one generator of 64 and XORs the LDS words of its support, all rw words at
+// once. So neither the bit columns nor their gathers pass through memory: the
+// former kernels wrote the columns out and gathered 512 bytes per support
+// qubit from L2, with 64 registers of words per lane (two waves per SIMD), and
+// stored 16 bytes to each of 64 lines at a time. Here a lane's words of one
+// row word are adjacent over the lanes (layouts 4, 2), or after a transpose
+// over the rows (layouts 1, 0), so stores are 256- or 512-byte runs. Bound by
+// vector instructions (the transposes) and LDS gathers. Row-major C and B^T at
+// n = 300 (45150 generators, 1000 observables, 10^4 samples, 62 MB out), bit
+// columns included: 50 -> 24 us; at n = 1000 (10^5, 2000, 10^4; 150 MB): 107
+// -> 76 us; 10 qubits, 55 generators: 23 -> 7 us.
+// Transposes the N x N block that N adjacent lanes hold in N pieces of 16 bytes
+// (lane q, piece p) <-> (lane p, piece q), N = 2 or 4.
+template <int N>
+__device__ __forceinline__ void lane_transpose(u32x4 (&p)[N], int lane) {
+#pragma unroll
+    for (int st = 1; st < N; st *= 2) {
+        const bool up = (lane & st) != 0;
+#pragma unroll
+        for (int a = 0; a < N; ++a) {
+            if (a & st) continue;
+            u32x4 &lo = p[a], &hi = p[a + st];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t give = up ? lo[d] : hi[d];
+                const uint32_t got = st == 1 ? lane_xor<1>(give) : lane_xor<2>(give);
+                lo[d] = up ? got : lo[d];
+                hi[d] = up ? hi[d] : got;
+            }
+        }
+    }
+}
+
+// Stores each lane's RW words (row words rw0 .. of generator j0 + lane, rows of
+// Rw words, an even number) with runs of 16 N bytes, N lanes to a run: the
+// cache takes one request per run, and single words of 64 rows at a time are
+// bound by their requests.
+template <int RW, int N>
+__device__ __forceinline__ void store_rows(const uint64_t (&x)[RW], uint64_t IQP_GLOBAL *out,
+                                           int64_t j0, int64_t Rw, int64_t rw0, int lane) {
+#pragma unroll
+    for (int b = 0; b < RW / (2 * N); ++b) {  // runs of 2 N words
+        u32x4 p[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const uint64_t u = x[2 * N * b + 2 * q], v = x[2 * N * b + 2 * q + 1];
+            p[q] = (u32x4){(uint32_t)u, (uint32_t)(u >> 32), (uint32_t)v, (uint32_t)(v >> 32)};
+        }
+        lane_transpose<N>(p, lane);
+        const int64_t w = rw0 + 2 * N * b + 2 * (lane % N);
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            if (w < Rw)
+                *reinterpret_cast<u32x4 IQP_GLOBAL *>(out + (j0 + lane - lane % N + q) * Rw + w) =
+                    p[q];
+    }
+}
+
+template <int LAYOUT, int RW>
+__device__ __forceinline__ void parity_rows(const ParityArgs &a, int64_t blk,
+                                            uint64_t *__restrict__ Xs) {
+    constexpr int ST = parity_stride(RW);
+    uint64_t IQP_GLOBAL *__restrict__ out = gptr(a.out);
+    const int64_t Rw = a.Rw, Gw = a.Gw;
+    const int W = a.W, lane = threadIdx.x & 63, wv = wave_id();
+    const int64_t ngc = ceil_div(Gw, a.gpb);
+    const int64_t rc = blk / ngc, gc = blk - rc * ngc;
+    const int64_t rw0 = rc * RW;
+    {
+        const uint64_t IQP_GLOBAL *rows = gptr(a.rows);
+        const int units = W * RW;
+        // unit u: row word u / W, qubit word u % W; four loads in flight
+        for (int u0 = wv; u0 < units; u0 += 16) {
+            uint64_t v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int u = u0 + 4 * q;
+                const int i = u / W, w = u - i * W;
+                const int64_t row = (rw0 + i) * 64 + lane;
+                v[q] = u < units && row < a.R ? rows[row * W + w] : 0ull;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int u = u0 + 4 * q;
+                if (u >= units) break;  // uniform over the wave
+                const int i = u / W, w = u - i * W;
+                Xs[(w * 64 + lane) * ST + i] = transpose64(v[q], lane);
+            }
+        }
+        if ((int)threadIdx.x < RW) Xs[64 * W * ST + threadIdx.x] = 0ull;
+    }
+    __syncthreads();
+    const int64_t g1 = (gc + 1) * a.gpb < Gw ? (gc + 1) * a.gpb : Gw;
+    for (int64_t gb = gc * a.gpb + wv; gb < g1; gb += 4) {
+        const i32x4 IQP_GLOBAL *sp =
+            reinterpret_cast<const i32x4 IQP_GLOBAL *>(gptr(a.sup) + (gb * 64 + lane) * kSupCap);
+        const i32x4 s0 = sp[0], s1 = sp[1];
+        const int32_t sv[kSupCap] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+        uint64_t x[RW];
+#pragma unroll
+        for (int i = 0; i < RW; ++i) x[i] = 0ull;
+#pragma unroll
+        for (int k = 0; k < kSupCap; ++k) {
+            if (__ballot(sv[k] >= 0) == 0ull) break;  // lists fill from entry 0
+            const uint64_t *col = Xs + (sv[k] >= 0 ? sv[k] : 64 * W) * ST;
+#pragma unroll
+            for (int i = 0; i < RW; ++i) x[i] ^= col[i];
+        }
+        if (sv[0] == -2) {  // heavier than the list: its bit row
+            for (int w = 0; w < W; ++w) {
+                uint64_t bits = gptr(a.gens)[(gb * 64 + lane) * W + w];
+                while (bits) {
+                    const uint64_t *col = Xs + (w * 64 + __builtin_ctzll(bits)) * ST;
+                    bits &= bits - 1;
+#pragma unroll
+                    for (int i = 0; i < RW; ++i) x[i] ^= col[i];
+                }
+            }
+        }
+        if constexpr (LAYOUT == 3 && RW >= 4) {
+            if ((Rw & 1) == 0) {
+                store_rows<RW, RW >= 8 ? 4 : 2>(x, out, gb * 64, Rw, rw0, lane);
+                continue;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int64_t rw = rw0 + i;
+            if (rw >= Rw) break;  // uniform over the wave
+            if (LAYOUT == 4) {
+                out[(rw * Gw + gb) * 64 + lane] = x[i];
+            } else if (LAYOUT == 3) {
+                out[(gb * 64 + lane) * Rw + rw] = x[i];
+            } else if (LAYOUT == 2) {
+                out[((gb * 2 + (lane >> 5)) * Rw + rw) * 32 + (lane & 31)] = x[i];
+            } else {
+                const uint64_t y = transpose64(x[i], lane);
+                const int64_t row = rw * 64 + lane;
+                if (LAYOUT == 1) {
+                    if (row < a.R_out) out[((row >> 5) * Gw + gb) * 32 + (lane & 31)] = y;
+                } else {
+                    if (row < a.R_out) out[row * Gw + gb] = y;
+                }
+            }
+        }
+    }
+}
+
+template <int LAYOUT>
+__device__ __forceinline__ void parity_body(const ParityArgs &a, int64_t blk) {
+    extern __shared__ uint64_t parity_lds[];
+    if (a.when && chain_on(a.gate) != (a.when == 2)) return;
+    if (a.rw == 16) parity_rows<LAYOUT, 16>(a, blk, parity_lds);
+    else if (a.rw == 8) parity_rows<LAYOUT, 8>(a, blk, parity_lds);
+    else if (a.rw == 4) parity_rows<LAYOUT, 4>(a, blk, parity_lds);
+    else if (a.rw == 2) parity_rows<LAYOUT, 2>(a, blk, parity_lds);
+    else parity_rows<LAYOUT, 1>(a, blk, parity_lds);
 }
 
 hipError_t launch_support(const LaunchCtx &lc, const SupportArgs &a) {
     return plain_launch<SupportArgs, support_body>(lc, KF_PARITY, a, blocks_of(a));
 }
 
-hipError_t launch_parity_bs(const LaunchCtx &lc, int layout, const ParityArgs &a) {
+// Rows of many words: the bit columns, then the kernel that gathers them.
+template <int LAYOUT>
+static hipError_t parity_one(const LaunchCtx &lc, const ParityArgs &a) {
     const int64_t nb = blocks_of(a);
-    if (layout == 0) return plain_launch<ParityArgs, parity_bs_body<0>>(lc, KF_PARITY, a, nb);
-    if (layout == 1) return plain_launch<ParityArgs, parity_bs_body<1>>(lc, KF_PARITY, a, nb);
-    if (layout == 2) return plain_launch<ParityArgs, parity_bs_body<2>>(lc, KF_PARITY, a, nb);
-    if (layout == 3) return plain_launch<ParityArgs, parity_bs_body<3>>(lc, KF_PARITY, a, nb);
-    if (layout == 4) return plain_launch<ParityArgs, parity_bs_body<4>>(lc, KF_PARITY, a, nb);
+    if (a.rw) return plain_launch<ParityArgs, parity_body<LAYOUT>>(lc, KF_PARITY, a, nb, lds_of(a));
+    const BitsliceArgs b = columns_of(a);
+    const hipError_t e = plain_launch<BitsliceArgs, bitslice_body>(lc, KF_PARITY, b, blocks_of(b));
+    if (e != hipSuccess) return e;
+    return plain_launch<ParityArgs, parity_bs_body<LAYOUT>>(lc, KF_PARITY, a, nb);
+}
+
+hipError_t launch_parity(const LaunchCtx &lc, int layout, const ParityArgs &a) {
+    if (layout == 0) return parity_one<0>(lc, a);
+    if (layout == 1) return parity_one<1>(lc, a);
+    if (layout == 2) return parity_one<2>(lc, a);
+    if (layout == 3) return parity_one<3>(lc, a);
+    if (layout == 4) return parity_one<4>(lc, a);
     return hipErrorInvalidValue;
+}
+
+template <int LA, int LB>
+static hipError_t parity_pair(const LaunchCtx &lc, const ParityArgs &a, const ParityArgs &b) {
+    if (!a.rw || !b.rw) {
+        const hipError_t e = parity_one<LA>(lc, a);
+        return e != hipSuccess ? e : parity_one<LB>(lc, b);
+    }
+    const size_t la = lds_of(a), lb = lds_of(b);
+    return pair_launch<ParityArgs, parity_body<LA>, ParityArgs, parity_body<LB>>(
+        lc, KF_PARITY, a, blocks_of(a), b, blocks_of(b), la > lb ? la : lb);
+}
+
+hipError_t launch_parity2(const LaunchCtx &lc, int la, const ParityArgs &a, int lb,
+                          const ParityArgs &b) {
+    if (la == 1 && lb == 1) return parity_pair<1, 1>(lc, a, b);
+    if (la == 4 && lb == 4) return parity_pair<4, 4>(lc, a, b);
+    if (la == 0 && lb == 3) return parity_pair<0, 3>(lc, a, b);
+    if (la == 1 && lb == 2) return parity_pair<1, 2>(lc, a, b);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_prep(const LaunchCtx &lc, const ThetaArgs &a, const SupportArgs &b) {
+    return pair_launch<ThetaArgs, theta_prep_body, SupportArgs, support_body>(
+        lc, KF_THETA, a, blocks_of(a), b, blocks_of(b));
 }
 
 // ---------------------------------------------------------------------------
@@ -964,8 +1162,12 @@ __device__ __forceinline__ void epilogue_body(const EpiArgs &a, int64_t blk) {
     sc = block_sum_256(sc, sh);
     sc2 = block_sum_256(sc2, sh);
     if (threadIdx.x == 0) {
-        part[(k * nchunk + ch) * 2 + 0] = sc;
-        part[(k * nchunk + ch) * 2 + 1] = sc2;
+        if (nchunk == 1) {
+            finalize_store(a.fin, k, sc, sc2);
+        } else {
+            part[(k * nchunk + ch) * 2 + 0] = sc;
+            part[(k * nchunk + ch) * 2 + 1] = sc2;
+        }
     }
 }
 
@@ -975,10 +1177,7 @@ hipError_t launch_epilogue(const LaunchCtx &lc, const EpiArgs &a) {
 
 __device__ __forceinline__ void finalize_body(const FinArgs &a, int64_t blk) {
     const double IQP_GLOBAL *__restrict__ part = gptr(a.part);
-    double IQP_GLOBAL *__restrict__ mean = gptr(a.mean);
-    double IQP_GLOBAL *__restrict__ stderr_ = gptr(a.stderr_);
-    double IQP_GLOBAL *__restrict__ rowsum = gptr(a.rowsum);
-    const int64_t s = a.s, nchunk = ceil_div(s, kEpiChunk);
+    const int64_t nchunk = ceil_div(a.s, kEpiChunk);
     const int64_t k = blk * 256 + threadIdx.x;
     if (k >= a.l) return;
     double sc = 0.0, sc2 = 0.0;
@@ -986,15 +1185,7 @@ __device__ __forceinline__ void finalize_body(const FinArgs &a, int64_t blk) {
         sc += part[(k * nchunk + ch) * 2 + 0];
         sc2 += part[(k * nchunk + ch) * 2 + 1];
     }
-    const double S = (double)s;
-    const double mu = sc / S;
-    const double var = sc2 / S - mu * mu;
-    if (mean) mean[k] = mu;
-    if (stderr_) stderr_[k] = sqrt((var > 0.0 ? var : 0.0) / S);
-    if (rowsum) {
-        rowsum[2 * k + 0] = sc;
-        rowsum[2 * k + 1] = sc2;
-    }
+    finalize_store(a, k, sc, sc2);
 }
 
 hipError_t launch_finalize(const LaunchCtx &lc, const FinArgs &a) {
@@ -1044,8 +1235,9 @@ __device__ __forceinline__ void coef_plain_body(const CoefArgs &a, int64_t blk) 
     coef_rowscale(a.sq, a.nf, k, al, 0.0);
 }
 
-hipError_t launch_coef_plain(const LaunchCtx &lc, const CoefArgs &a) {
-    return plain_launch<CoefArgs, coef_plain_body>(lc, KF_WEIGHTS, a, blocks_of(a));
+hipError_t launch_prep(const LaunchCtx &lc, const CoefArgs &a, const SupportArgs &b) {
+    return pair_launch<CoefArgs, coef_plain_body, SupportArgs, support_body>(
+        lc, KF_WEIGHTS, a, blocks_of(a), b, blocks_of(b));
 }
 
 // One block per 64 observables x 64 samples: S values are staged in LDS and
@@ -2382,33 +2574,34 @@ hipError_t launch_grad_reduce(const LaunchCtx &lc, const GradArgs &a) {
 // Batched launches of the per-step bodies.
 template <typename A, void (*F)(const A &, int64_t)>
 static void batched(const LaunchCtx &lc, const void *args, const int64_t *off, int np,
-                    int64_t total) {
+                    int64_t total, size_t lds = 0) {
     for (int64_t base = 0; base < total; base += kMaxBlocks) {
         const int64_t n = total - base < kMaxBlocks ? total - base : kMaxBlocks;
-        hipLaunchKernelGGL((batched_kernel<A, F>), dim3((unsigned)n), dim3(256), 0, lc.stream,
+        hipLaunchKernelGGL((batched_kernel<A, F>), dim3((unsigned)n), dim3(256), lds, lc.stream,
                            static_cast<const A *>(args), off, np, base);
     }
 }
 
 hipError_t launch_batched(const LaunchCtx &lc, int kind, const void *args, const int64_t *off,
-                          int np, int64_t total) {
+                          int np, int64_t total, size_t lds) {
     if (total <= 0) return hipSuccess;
     // the gate lists and the gradient sums take more blocks per gate than the
     // other steps, so they may take several launches
     if (np < 1 || (total > kMaxBlocks && kind != SK_GRAD && kind != SK_GATELIST))
         return hipErrorInvalidConfiguration;
-    static const int family[SK_COUNT] = {KF_THETA, KF_PARITY,  KF_PARITY,  KF_PARITY,
-                                         KF_PARITY, KF_EPI,    KF_FIN,     KF_WEIGHTS,
-                                         KF_WEIGHTS, KF_GRAD,  KF_PARITY, KF_PARITY};
+    static const int family[SK_COUNT] = {KF_THETA, KF_PARITY,  KF_PARITY, KF_PARITY, KF_EPI, KF_FIN,
+                                         KF_WEIGHTS, KF_WEIGHTS, KF_GRAD, KF_PARITY, KF_PARITY,
+                                         KF_PARITY, KF_PARITY};
     if (kind < 0 || kind >= SK_COUNT) return hipErrorInvalidValue;
     hipEvent_t ev;
     timed_begin(lc, family[kind], &ev);
     switch (kind) {
         case SK_THETA: batched<ThetaArgs, theta_prep_body>(lc, args, off, np, total); break;
         case SK_BITSLICE: batched<BitsliceArgs, bitslice_body>(lc, args, off, np, total); break;
-        case SK_PARITY0: batched<ParityArgs, parity_bs_body<0>>(lc, args, off, np, total); break;
-        case SK_PARITY1: batched<ParityArgs, parity_bs_body<1>>(lc, args, off, np, total); break;
-        case SK_PARITY4: batched<ParityArgs, parity_bs_body<4>>(lc, args, off, np, total); break;
+        case SK_PARITY1: batched<ParityArgs, parity_body<1>>(lc, args, off, np, total, lds); break;
+        case SK_PARITY4: batched<ParityArgs, parity_body<4>>(lc, args, off, np, total, lds); break;
+        case SK_COLPARITY1: batched<ParityArgs, parity_bs_body<1>>(lc, args, off, np, total); break;
+        case SK_COLPARITY4: batched<ParityArgs, parity_bs_body<4>>(lc, args, off, np, total); break;
         case SK_EPI: batched<EpiArgs, epilogue_body>(lc, args, off, np, total); break;
         case SK_FIN: batched<FinArgs, finalize_body>(lc, args, off, np, total); break;
         case SK_COEF: batched<CoefArgs, coef_plain_body>(lc, args, off, np, total); break;
@@ -2584,8 +2777,9 @@ __device__ __forceinline__ void bitflip_prep_body(const BitflipPrepArgs &a, int6
     gptr(a.enc)[j] = copysign(c == 0.0 ? (double)INFINITY : -log(fabs(c)), c);
 }
 
-hipError_t launch_bitflip_prep(const LaunchCtx &lc, const BitflipPrepArgs &a) {
-    return plain_launch<BitflipPrepArgs, bitflip_prep_body>(lc, KF_THETA, a, blocks_of(a));
+hipError_t launch_prep(const LaunchCtx &lc, const BitflipPrepArgs &a, const SupportArgs &b) {
+    return pair_launch<BitflipPrepArgs, bitflip_prep_body, SupportArgs, support_body>(
+        lc, KF_THETA, a, blocks_of(a), b, blocks_of(b));
 }
 
 // One wave per observable k: lane v walks gate words v, v + 64, ... of the

@@ -116,37 +116,43 @@ inline ThetaArgs theta_args(const Plan &P, const double *theta, void *ws) {
                      at<float>(ws, P.o_t32),
                      nullptr};
 }
-inline BitsliceArgs bitslice_ops_args(const Plan &P, const uint64_t *ops, void *ws) {
-    return BitsliceArgs{ops, P.l, (int)P.W, P.lda, at<uint64_t>(ws, P.o_xa)};
-}
-inline BitsliceArgs bitslice_samples_args(const Plan &P, const uint64_t *samples, void *ws) {
-    return BitsliceArgs{samples, P.s, (int)P.W, P.ldz, at<uint64_t>(ws, P.o_xz)};
-}
 // support lists of the generators (m_pad rows)
 inline SupportArgs support_args(const Plan &P, const uint64_t *gens, void *ws) {
     return SupportArgs{gens, P.m, (int)P.W, P.m_pad, at<int32_t>(ws, P.o_sup)};
 }
-// C and B (tiled32) for the forward
-inline ParityArgs parity_c_args(const Plan &P, const uint64_t *gens, void *ws) {
-    return ParityArgs{gens,    at<int32_t>(ws, P.o_sup), P.m,   (int)P.W,
-                      at<uint64_t>(ws, P.o_xa), P.l_pad / 64, P.lda, P.l_pad,
-                      P.mw,    at<uint64_t>(ws, P.o_cbits)};
+// Parities of the generators against the observables or the samples into the
+// buffer at o_out, for row_words words of 64 rows (the first r_out rows in the
+// layouts of rows).
+inline ParityArgs parity_ops_args(const Plan &P, const uint64_t *gens, const uint64_t *ops,
+                                  void *ws, int64_t r_out, size_t o_out) {
+    return parity_args(ops, P.l, gens, at<int32_t>(ws, P.o_sup), P.m, (int)P.W,
+                       at<uint64_t>(ws, P.o_xa), P.lda, P.l_pad / 64, r_out, P.mw,
+                       at<uint64_t>(ws, o_out));
 }
-inline ParityArgs parity_b_args(const Plan &P, const uint64_t *gens, void *ws) {
-    return ParityArgs{gens,    at<int32_t>(ws, P.o_sup), P.m,   (int)P.W,
-                      at<uint64_t>(ws, P.o_xz), P.s_pad / 64, P.ldz, P.s_pad,
-                      P.mw,    at<uint64_t>(ws, P.o_bbits)};
+inline ParityArgs parity_samples_args(const Plan &P, const uint64_t *gens,
+                                      const uint64_t *samples, void *ws, int64_t r_out,
+                                      size_t o_out) {
+    return parity_args(samples, P.s, gens, at<int32_t>(ws, P.o_sup), P.m, (int)P.W,
+                       at<uint64_t>(ws, P.o_xz), P.ldz, P.s_pad / 64, r_out, P.mw,
+                       at<uint64_t>(ws, o_out));
+}
+// C and B (tiled32) for the forward
+inline ParityArgs parity_c_args(const Plan &P, const uint64_t *gens, const uint64_t *ops,
+                                void *ws) {
+    return parity_ops_args(P, gens, ops, ws, P.l_pad, P.o_cbits);
+}
+inline ParityArgs parity_b_args(const Plan &P, const uint64_t *gens, const uint64_t *samples,
+                                void *ws) {
+    return parity_samples_args(P, gens, samples, ws, P.s_pad, P.o_bbits);
 }
 // B^T and C^T (transposed word-major) for the backward
-inline ParityArgs parity_bt_args(const Plan &P, const uint64_t *gens, void *ws) {
-    return ParityArgs{gens,    at<int32_t>(ws, P.o_sup), P.m,   (int)P.W,
-                      at<uint64_t>(ws, P.o_xz), P.s_pad / 64, P.ldz, 0,
-                      P.mw,    at<uint64_t>(ws, P.o_btbits)};
+inline ParityArgs parity_bt_args(const Plan &P, const uint64_t *gens, const uint64_t *samples,
+                                 void *ws) {
+    return parity_samples_args(P, gens, samples, ws, 0, P.o_btbits);
 }
-inline ParityArgs parity_ct_args(const Plan &P, const uint64_t *gens, void *ws) {
-    return ParityArgs{gens,    at<int32_t>(ws, P.o_sup), P.m, (int)P.W,
-                      at<uint64_t>(ws, P.o_xa), P.lw,     P.lda, 0,
-                      P.mw,    at<uint64_t>(ws, P.o_ctbits)};
+inline ParityArgs parity_ct_args(const Plan &P, const uint64_t *gens, const uint64_t *ops,
+                                 void *ws) {
+    return parity_ops_args(P, gens, ops, ws, 0, P.o_ctbits);
 }
 inline FwdArgs fwd_args(const Plan &P, void *ws, int64_t splits) {
     return FwdArgs{at<uint64_t>(ws, P.o_cbits), at<uint64_t>(ws, P.o_bbits),
@@ -156,12 +162,13 @@ inline FwdArgs fwd_args(const Plan &P, void *ws, int64_t splits) {
                    P.l_pad,                     P.s_pad,
                    splits,                      at<float>(ws, P.o_E)};
 }
-inline EpiArgs epi_args(const Plan &P, void *ws, int64_t splits, float *phase_out) {
-    return EpiArgs{at<float>(ws, P.o_E), splits,   P.l, P.s, P.l_pad, P.s_pad,
-                   phase_out,            at<double>(ws, P.o_part)};
-}
 inline FinArgs fin_args(const Plan &P, void *ws, double *mean, double *se, double *rowsum) {
     return FinArgs{at<double>(ws, P.o_part), P.l, P.s, mean, se, rowsum};
+}
+inline EpiArgs epi_args(const Plan &P, void *ws, int64_t splits, float *phase_out,
+                        const FinArgs &fin) {
+    return EpiArgs{at<float>(ws, P.o_E), splits,   P.l, P.s, P.l_pad, P.s_pad,
+                   phase_out,            at<double>(ws, P.o_part), fin};
 }
 inline CoefArgs coef_args(const Plan &P, const double *grad_mean, void *ws) {
     const bool fx = P.prec == IQP_SPLIT3_BF16;

@@ -428,9 +428,15 @@ __device__ __forceinline__ void sparse_fwd_lut_body(const SparseFwdArgs &a, int6
     }
     __syncthreads();
     if (tid == 0) {
-        double IQP_GLOBAL *part = gptr(a.part) + (k * nchunk + ch) * 2;
-        part[0] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-        part[1] = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
+        sc = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+        sc2 = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
+        if (nchunk == 1) {
+            finalize_store(a.fin, k, sc, sc2);
+        } else {
+            double IQP_GLOBAL *part = gptr(a.part) + (k * nchunk + ch) * 2;
+            part[0] = sc;
+            part[1] = sc2;
+        }
     }
 }
 
@@ -658,9 +664,15 @@ __device__ __forceinline__ void chain_fwd_body(const ChainFwdArgs &a, int64_t bl
     __syncthreads();
     const int64_t c2 = ch * 2 + tid;  // the block's two epilogue chunks
     if (tid < 2 && c2 < nchunk) {
-        double IQP_GLOBAL *part = gptr(a.part) + (k * nchunk + c2) * 2;
-        part[0] = red[0][2 * tid] + red[0][2 * tid + 1];
-        part[1] = red[1][2 * tid] + red[1][2 * tid + 1];
+        sc = red[0][2 * tid] + red[0][2 * tid + 1];
+        sc2 = red[1][2 * tid] + red[1][2 * tid + 1];
+        if (nchunk == 1) {
+            finalize_store(a.fin, k, sc, sc2);
+        } else {
+            double IQP_GLOBAL *part = gptr(a.part) + (k * nchunk + c2) * 2;
+            part[0] = sc;
+            part[1] = sc2;
+        }
     }
 }
 
