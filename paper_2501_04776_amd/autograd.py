@@ -23,11 +23,16 @@ class IQPExpval(torch.autograd.Function):
         ctx.n_qubits = n_qubits
         ctx.precision = precision
         ctx.mark_non_differentiable(se)
+        # no zero tensor stands in for the missing gradient of se, so the
+        # backward has nothing to read back from the device
+        ctx.set_materialize_grads(False)
         return mean, se
 
     @staticmethod
     def backward(ctx, grad_mean, grad_se):
         theta, gens, ops, samples, ph = ctx.saved_tensors
+        if grad_mean is None:
+            return (None,) * 6
         if grad_se is not None and bool((grad_se != 0).any()):
             raise RuntimeError("the standard error is not differentiable")
         circ = api.Circuit(ctx.n_qubits, gens, theta.detach())
