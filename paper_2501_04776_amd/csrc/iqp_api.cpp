@@ -330,8 +330,9 @@ void make_plan(Plan &P, const PlanParts &parts, int64_t n, int64_t m, int64_t l,
         } else {
             P.o_s32 = carve(cur, (size_t)P.s_pad * P.l_pad * 4);
         }
-        // gate lists: counters and two entry arrays per 64 observables
-        P.o_gcnt = carve(cur, (size_t)P.lw * 4 * 4);
+        // gate lists: counters (and an 8-byte one of C's entries) and two entry
+        // arrays per 64 observables
+        P.o_gcnt = carve(cur, (size_t)P.lw * 4 * 4 + 8);
         P.o_glist = carve(cur, (size_t)P.lw * 2 * P.m_pad * 4);
         P.o_gpart = carve(cur, (size_t)P.tc.bsplits * (P.l_pad / (32 * P.tc.bfm)) * P.m_pad * 4);
     }
@@ -360,7 +361,7 @@ static void make_bitflip_plan(Plan &P, bool grad, int64_t n, int64_t m, int64_t 
     P.o_sup = carve(cur, (size_t)P.m_pad * kSupCap * 4);
     P.o_cbits = carve(cur, (size_t)P.l_pad * P.mw * 8);
     P.o_enc = carve(cur, (size_t)P.m_pad * 8);
-    P.o_stat = carve(cur, (size_t)P.l_pad * 2 * 8);
+    P.o_stat = carve(cur, (size_t)P.l_pad * 4 * 8);  // statistics, then gradient values
     P.o_rowsum = carve(cur, (size_t)P.l_pad * 8);  // the product, when only the gradient is asked
     if (grad) P.o_ctbits = carve(cur, (size_t)P.m_pad * P.lw * 8);
     P.total = cur;
@@ -626,13 +627,49 @@ static int run_backward(const Plan &P, const iqp_circuit *c, const uint64_t *ops
                 "sparse_finish");
         return IQP_OK;
     }
-    IQP_TRY(launch_weights(lc, weights_args(P, phase, ws)), "weights");
+    WeightsArgs wa = weights_args(P, phase, ws);
+    GateListArgs la = gate_list_args(P, ws, P.tc.bfm, P.tc.bfn);
+    BwdArgs ba = bwd_args(P, ws);
+    GradArgs ga = grad_args(P, ws, P.tc.bfm, grad_theta);
+    // FP32: the non-zero entries of C alone where they are few (chain_density
+    // at full wave slots), at most cap to a row. C row-major takes the space of
+    // the gate lists, the ranks that of the gradient partials and T that of the
+    // weights, each of which the other way writes after the count or not at all.
+    const bool chain = P.prec == IQP_FP32 && P.tc.bsplits <= kChainMaxSplits &&
+                       (double)P.l * (double)P.s * (double)P.m >= kChainTerms;
+    const int64_t cap = P.s_pad * P.l_pad / (P.l * P.tc.bsplits);
+    ChainGate gate;
+    if (chain) {
+        unsigned long long *nnz = reinterpret_cast<unsigned long long *>(
+            at<int32_t>(ws, P.o_gcnt) + 4 * P.lw);
+        gate.nnz = nnz;
+        gate.limit = (unsigned long long)((double)P.l * (double)P.m / 12.0);
+        IQP_TRY(launch_parity(lc, IQP_BITS_ROW_MAJOR,
+                              parity_ops_args(P, c->gens, ops, ws, P.l, P.o_glist)),
+                "parity(C, row-major)");
+        IQP_TRY(launch_rank(lc, RankArgs{at<uint64_t>(ws, P.o_glist), P.l, P.mw, cap,
+                                         at<uint32_t>(ws, P.o_gpart), nnz}),
+                "rank");
+        wa.gate = la.gate = ba.gate = ga.gate = gate;
+    }
+    IQP_TRY(launch_weights(lc, wa), "weights");
     IQP_TRY(launch_parity2(lc, kBitsWordMajor, parity_bt_args(P, c->gens, samples, ws),
                            kBitsWordMajor, parity_ct_args(P, c->gens, ops, ws)),
             "parity(B^T, C^T)");
-    IQP_TRY(launch_gate_list(lc, gate_list_args(P, ws, P.tc.bfm, P.tc.bfn)), "gate_list");
-    IQP_TRY(launch_phase_bwd(lc, P.prec, P.tc.bfm, P.tc.bfn, bwd_args(P, ws)), "phase_bwd");
-    IQP_TRY(launch_grad_reduce(lc, grad_args(P, ws, P.tc.bfm, grad_theta)), "grad_reduce");
+    IQP_TRY(launch_gate_list(lc, la), "gate_list");
+    IQP_TRY(launch_phase_bwd(lc, P.prec, P.tc.bfm, P.tc.bfn, ba), "phase_bwd");
+    IQP_TRY(launch_grad_reduce(lc, ga), "grad_reduce");
+    if (!chain) return IQP_OK;
+    IQP_TRY(launch_chain_bwd(lc, ChainBwdArgs{at<uint64_t>(ws, P.o_glist), P.mw, P.m_pad,
+                                              at<uint64_t>(ws, P.o_btbits), P.l, P.s, P.s_pad,
+                                              P.tc.bsplits, cap, phase, at<double>(ws, P.o_coef),
+                                              at<float>(ws, P.o_s32), gate}),
+            "chain_bwd");
+    IQP_TRY(launch_chain_grad(lc, ChainGradArgs{at<uint64_t>(ws, P.o_ctbits),
+                                                at<uint32_t>(ws, P.o_gpart),
+                                                at<float>(ws, P.o_s32), P.l, P.lw, P.m, P.m_pad,
+                                                P.mw, P.tc.bsplits, cap, grad_theta, gate}),
+            "chain_grad");
     return IQP_OK;
 }
 
@@ -900,24 +937,48 @@ int iqp_mmd_loss_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops,
     return run_backward(P, c, ops, samples, phi, true, ws, lc, grad_theta);
 }
 
-// Forward of a bitflip circuit into the plan's buffers (mean may be the
-// workspace's own slot).
-static int run_bitflip_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
-                               void *ws, const LaunchCtx &lc, double *mean, bool grad) {
-    IQP_TRY(launch_prep(lc, BitflipPrepArgs{c->theta, P.m, at<double>(ws, P.o_enc)},
-                        support_args(P, c->gens, ws)),
+// A bitflip circuit's forward into mean, or, with grad_mean, its gradient into
+// grad_theta.
+static int run_bitflip(const Plan &P, const iqp_circuit *c, const uint64_t *ops, void *ws,
+                       const LaunchCtx &lc, double *mean, const double *grad_mean,
+                       double *grad_theta) {
+    double *enc = at<double>(ws, P.o_enc), *stat = at<double>(ws, P.o_stat);
+    IQP_TRY(launch_prep(lc, BitflipPrepArgs{c->theta, P.m, enc}, support_args(P, c->gens, ws)),
             "bitflip_prep, support");
     const ParityArgs pc = parity_ops_args(P, c->gens, ops, ws, P.l_pad, P.o_cbits);
-    if (grad)
+    if (pc.rw) {
+        // the sums take the space of C, the dot products that of C^T
+        const int64_t ngc = ceil_div(pc.Gw, pc.gpb);
+        double *psum = at<double>(ws, P.o_cbits), *val = stat + 2 * P.l_pad;
+        int32_t *pcode = reinterpret_cast<int32_t *>(psum + ngc * P.l_pad);
+        IQP_TRY(launch_bitflip_sum(lc, BitflipSumArgs{pc, enc, P.l_pad, psum, pcode}),
+                "bitflip_sum");
+        IQP_TRY(launch_bitflip_finish(lc, BitflipFinishArgs{psum, pcode, ngc, P.l, P.l_pad, mean,
+                                                            grad_mean, stat, val}),
+                "bitflip_finish");
+        if (!grad_mean) return IQP_OK;
+        double *part = at<double>(ws, P.o_ctbits);
+        IQP_TRY(launch_bitflip_dot(lc, BitflipDotArgs{pc, enc, stat, val, P.l, P.m_pad, part}),
+                "bitflip_dot");
+        IQP_TRY(launch_bitflip_chain(lc, BitflipChainArgs{part, c->theta, ceil_div(pc.Rw, pc.rw),
+                                                          P.m, P.m_pad, grad_theta}),
+                "bitflip_chain");
+        return IQP_OK;
+    }
+    if (grad_mean)
         IQP_TRY(launch_parity2(lc, IQP_BITS_TILED32, pc, IQP_BITS_TILED32_T,
                                parity_ops_args(P, c->gens, ops, ws, 0, P.o_ctbits)),
                 "parity(C, C^T)");
     else
         IQP_TRY(launch_parity(lc, IQP_BITS_TILED32, pc), "parity(C)");
-    IQP_TRY(launch_bitflip_fwd(lc, BitflipFwdArgs{at<uint64_t>(ws, P.o_cbits),
-                                                   at<double>(ws, P.o_enc), P.l, P.mw, mean,
-                                                   nullptr, at<double>(ws, P.o_stat)}),
+    IQP_TRY(launch_bitflip_fwd(lc, BitflipFwdArgs{at<uint64_t>(ws, P.o_cbits), enc, P.l, P.mw,
+                                                  mean ? mean : at<double>(ws, P.o_rowsum),
+                                                  nullptr, stat}),
             "bitflip_fwd");
+    if (!grad_mean) return IQP_OK;
+    IQP_TRY(launch_bitflip_grad(lc, BitflipGradArgs{at<uint64_t>(ws, P.o_ctbits), enc, c->theta,
+                                                    stat, grad_mean, P.m, P.lw, grad_theta}),
+            "bitflip_grad");
     return IQP_OK;
 }
 
@@ -933,7 +994,7 @@ int iqp_bitflip_expval(const iqp_circuit *c, int64_t l, const uint64_t *ops, dou
     make_bitflip_plan(P, false, c->n_qubits, c->n_gates, l);
     if ((st = check_ws(P, ws, ws_bytes))) return st;
     if ((st = check_device())) return st;
-    return run_bitflip_forward(P, c, ops, ws, make_ctx(stream), mean, false);
+    return run_bitflip(P, c, ops, ws, make_ctx(stream), mean, nullptr, nullptr);
 }
 
 int iqp_bitflip_expval_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops,
@@ -950,15 +1011,7 @@ int iqp_bitflip_expval_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops
     make_bitflip_plan(P, true, c->n_qubits, c->n_gates, l);
     if ((st = check_ws(P, ws, ws_bytes))) return st;
     if ((st = check_device())) return st;
-    LaunchCtx lc = make_ctx(stream);
-    st = run_bitflip_forward(P, c, ops, ws, lc, at<double>(ws, P.o_rowsum), true);
-    if (st) return st;
-    IQP_TRY(launch_bitflip_grad(lc, BitflipGradArgs{at<uint64_t>(ws, P.o_ctbits),
-                                                     at<double>(ws, P.o_enc), c->theta,
-                                                     at<double>(ws, P.o_stat), grad_mean, P.m,
-                                                     P.lw, grad_theta}),
-            "bitflip_grad");
-    return IQP_OK;
+    return run_bitflip(P, c, ops, ws, make_ctx(stream), nullptr, grad_mean, grad_theta);
 }
 
 const char *iqp_strerror(int status) {

@@ -222,6 +222,24 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+// Sums of two doubles per thread over a 256-thread block, in a fixed order:
+// a butterfly in each wave, then the four waves. Thread 0 has the results.
+__device__ __forceinline__ void block_sum2_256(double &a, double &b, double (*sh)[4]) {
+#pragma unroll
+    for (int st = 32; st >= 1; st >>= 1) {
+        a += __shfl_xor(a, st, 64);
+        b += __shfl_xor(b, st, 64);
+    }
+    const int wv = wave_id();
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][wv] = a;
+        sh[1][wv] = b;
+    }
+    __syncthreads();
+    a = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
+    b = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
+}
+
 // Mean and standard error of observable k from its sums of cos and cos^2.
 __device__ __forceinline__ void finalize_store(const FinArgs &a, int64_t k, double sc, double sc2) {
     const double S = (double)a.s;

@@ -226,9 +226,53 @@ struct ChainFwdArgs {
     FinArgs fin;
     ChainGate gate;
 };
+// The FP32 backward over the non-zero entries: crm C row-major (mw words per
+// row), rank[k][w] = entries of row k before word w; *nnz counts all, or stays
+// past any limit when a row holds more than cap entries.
+struct RankArgs {
+    const uint64_t *crm;
+    int64_t l, mw, cap;
+    uint32_t *rank;
+    unsigned long long *nnz;
+};
+inline int64_t blocks_of(const RankArgs &a) { return a.l; }
+// T[(ks l + k) cap + position of gate j in row k] = the sum over the samples of
+// split ks of S_ki (-1)^{b_ij}.
+struct ChainBwdArgs {
+    const uint64_t *crm;
+    int64_t mw, m_pad;
+    const uint64_t *btbits;  // word-major
+    int64_t l, s, s_pad, ksplits, cap;
+    const float *phase;
+    const double *coef;
+    float *T;
+    ChainGate gate;
+};
+inline int64_t blocks_of(const ChainBwdArgs &a) { return a.l * a.ksplits; }
+struct ChainGradArgs {
+    const uint64_t *ctbits;  // word-major
+    const uint32_t *rank;
+    const float *T;
+    int64_t l, lw, m, m_pad, mw, ksplits, cap;
+    double *grad;
+    ChainGate gate;
+};
+constexpr int64_t kChainMaxSplits = 8;
+inline int64_t blocks_of(const ChainGradArgs &a) { return a.mw; }
 constexpr int64_t kChainChunk = 2 * kEpiChunk;  // samples per block
 inline int64_t blocks_of(const ChainFwdArgs &a) { return a.l * ceil_div(a.s, kChainChunk); }
-inline int64_t blocks_of(const EpiArgs &a) { return a.l * ceil_div(a.s, kEpiChunk); }
+// A wave per (observable, chunk) unit where that makes several rounds of eight
+// waves per SIMD, a block per unit before (10^4 units: 45 us by wave, 38 by
+// block; 10^5: 195 and 224).
+__host__ __device__ inline bool epilogue_by_wave(const EpiArgs &a) {
+    return a.l * ceil_div(a.s, kEpiChunk) >= 64 * kWaveSlots;
+}
+// (more units than 2^24 - 1 blocks were never accepted, and a unit's number
+// fits 32 bits)
+inline int64_t blocks_of(const EpiArgs &a) {
+    const int64_t units = a.l * ceil_div(a.s, kEpiChunk);
+    return epilogue_by_wave(a) && units < ((int64_t)1 << 24) ? ceil_div(units, 4) : units;
+}
 
 inline int64_t blocks_of(const FinArgs &a) {
     return a.s <= kEpiChunk ? 0 : ceil_div(a.l, 256);
@@ -264,6 +308,7 @@ struct WeightsArgs {
     float *s32;
     int32_t *nf;
     double *sq;
+    ChainGate gate = {};  // FP32 only, as in the steps below
 };
 inline int64_t blocks_of(const WeightsArgs &a) { return (a.s_pad / 64) * (a.l_pad / 64); }
 
@@ -284,6 +329,7 @@ struct GateListArgs {
     int cw;     // 64-row words per block: cf / 2
     int split;  // classes by half (1) or one class (0)
     int32_t *gcnt, *glist;
+    ChainGate gate = {};
 };
 constexpr int64_t kListSeg = 1024;  // gates per block of the list kernel
 inline int64_t blocks_of(const GateListArgs &a) {
@@ -306,6 +352,7 @@ struct BwdArgs {
     const int32_t *nf;
     int64_t obgroup;    // observable blocks per unit group (unit order only)
     const int32_t *gcnt, *glist;
+    ChainGate gate = {};
 };
 // How the backward of a form runs its tile configuration bfm x bfn: gates of a
 // wave in column blocks of 32 (fn), and whether the lists are split by the
@@ -333,6 +380,7 @@ struct GradArgs {
     double *grad;
     const uint64_t *ctbits;
     int cw;
+    ChainGate gate = {};
 };
 inline int64_t blocks_of(const GradArgs &a) { return ceil_div(a.m, 64); }
 
@@ -360,6 +408,42 @@ struct BitflipGradArgs {
     double *grad;
 };
 inline int64_t blocks_of(const BitflipGradArgs &a) { return ceil_div(a.m, 256); }
+
+// The same from the parities in registers (rows of fewer than kColumnWords
+// words): par names the observables' rows and the blocking; sums per gate
+// chunk psum / pcode [ngc][l_pad], dot products per observable chunk part
+// [nrc][m_pad].
+struct BitflipSumArgs {
+    ParityArgs par;
+    const double *enc;
+    int64_t l_pad;
+    double *psum;
+    int32_t *pcode;
+};
+inline size_t lds_of(const BitflipSumArgs &a) {
+    const size_t sums = (size_t)64 * a.par.rw * 12, bits = lds_of(a.par);
+    return sums > bits ? sums : bits;
+}
+struct BitflipFinishArgs {
+    const double *psum;
+    const int32_t *pcode;
+    int64_t ngc, l, l_pad;
+    double *mean;
+    const double *grad_mean;  // NULL: forward only
+    double *stat, *val;       // [l][2] each
+};
+struct BitflipDotArgs {
+    ParityArgs par;
+    const double *enc, *stat, *val;
+    int64_t l, m_pad;
+    double *part;
+};
+inline size_t lds_of(const BitflipDotArgs &a) { return lds_of(a.par) + (size_t)a.par.rw * 65 * 8; }
+struct BitflipChainArgs {
+    const double *part, *theta;
+    int64_t nrc, m, m_pad;
+    double *grad;
+};
 
 // Where the sparse kernels read the sample parities b_ij of generator j
 // (bit i % 64 of word i / 64):
@@ -454,6 +538,9 @@ hipError_t launch_phase_bwd(const LaunchCtx &lc, int prec, int fm, int fn, const
 hipError_t launch_grad_reduce(const LaunchCtx &lc, const GradArgs &a);
 hipError_t launch_count(const LaunchCtx &lc, const CountArgs &a);
 hipError_t launch_chain_fwd(const LaunchCtx &lc, const ChainFwdArgs &a);
+hipError_t launch_rank(const LaunchCtx &lc, const RankArgs &a);
+hipError_t launch_chain_bwd(const LaunchCtx &lc, const ChainBwdArgs &a);
+hipError_t launch_chain_grad(const LaunchCtx &lc, const ChainGradArgs &a);
 hipError_t launch_sparse_fwd(const LaunchCtx &lc, const SparseFwdArgs &a);
 hipError_t launch_sparse_bound(const LaunchCtx &lc, const SparseBoundArgs &a);
 hipError_t launch_sparse_bwd(const LaunchCtx &lc, const SparseBwdArgs &a);
@@ -461,6 +548,10 @@ hipError_t launch_sparse_finish(const LaunchCtx &lc, const SparseFinishArgs &a);
 hipError_t launch_indep_slice(const LaunchCtx &lc, const IndepSliceArgs &a);
 hipError_t launch_bitflip_fwd(const LaunchCtx &lc, const BitflipFwdArgs &a);
 hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a);
+hipError_t launch_bitflip_sum(const LaunchCtx &lc, const BitflipSumArgs &a);
+hipError_t launch_bitflip_finish(const LaunchCtx &lc, const BitflipFinishArgs &a);
+hipError_t launch_bitflip_dot(const LaunchCtx &lc, const BitflipDotArgs &a);
+hipError_t launch_bitflip_chain(const LaunchCtx &lc, const BitflipChainArgs &a);
 
 // Batched launches: `args` is a device array of np argument structs of the
 // step's type and `off` a device array of np + 1 prefix sums of their block

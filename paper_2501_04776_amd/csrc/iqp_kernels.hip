@@ -339,67 +339,83 @@ __device__ __forceinline__ void store_rows(const uint64_t (&x)[RW], uint64_t IQP
     }
 }
 
+// Stages the bit columns of row words rw0 .. rw0 + RW - 1 in Xs.
+template <int RW>
+__device__ __forceinline__ void parity_stage(const ParityArgs &a, int64_t rw0,
+                                             uint64_t *__restrict__ Xs) {
+    constexpr int ST = parity_stride(RW);
+    const uint64_t IQP_GLOBAL *rows = gptr(a.rows);
+    const int W = a.W, lane = threadIdx.x & 63, wv = wave_id();
+    const int units = W * RW;
+    // unit u: row word u / W, qubit word u % W; four loads in flight
+    for (int u0 = wv; u0 < units; u0 += 16) {
+        uint64_t v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int u = u0 + 4 * q;
+            const int i = u / W, w = u - i * W;
+            const int64_t row = (rw0 + i) * 64 + lane;
+            v[q] = u < units && row < a.R ? rows[row * W + w] : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int u = u0 + 4 * q;
+            if (u >= units) break;  // uniform over the wave
+            const int i = u / W, w = u - i * W;
+            Xs[(w * 64 + lane) * ST + i] = transpose64(v[q], lane);
+        }
+    }
+    if ((int)threadIdx.x < RW) Xs[64 * W * ST + threadIdx.x] = 0ull;
+    __syncthreads();
+}
+
+// The parities of generator 64 gb + lane against the staged rows.
+template <int RW>
+__device__ __forceinline__ void parity_gather(const ParityArgs &a, int64_t gb, int lane,
+                                              const uint64_t *__restrict__ Xs,
+                                              uint64_t (&x)[RW]) {
+    constexpr int ST = parity_stride(RW);
+    const int W = a.W;
+    const i32x4 IQP_GLOBAL *sp =
+        reinterpret_cast<const i32x4 IQP_GLOBAL *>(gptr(a.sup) + (gb * 64 + lane) * kSupCap);
+    const i32x4 s0 = sp[0], s1 = sp[1];
+    const int32_t sv[kSupCap] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+#pragma unroll
+    for (int i = 0; i < RW; ++i) x[i] = 0ull;
+#pragma unroll
+    for (int k = 0; k < kSupCap; ++k) {
+        if (__ballot(sv[k] >= 0) == 0ull) break;  // lists fill from entry 0
+        const uint64_t *col = Xs + (sv[k] >= 0 ? sv[k] : 64 * W) * ST;
+#pragma unroll
+        for (int i = 0; i < RW; ++i) x[i] ^= col[i];
+    }
+    if (sv[0] == -2) {  // heavier than the list: its bit row
+        for (int w = 0; w < W; ++w) {
+            uint64_t bits = gptr(a.gens)[(gb * 64 + lane) * W + w];
+            while (bits) {
+                const uint64_t *col = Xs + (w * 64 + __builtin_ctzll(bits)) * ST;
+                bits &= bits - 1;
+#pragma unroll
+                for (int i = 0; i < RW; ++i) x[i] ^= col[i];
+            }
+        }
+    }
+}
+
 template <int LAYOUT, int RW>
 __device__ __forceinline__ void parity_rows(const ParityArgs &a, int64_t blk,
                                             uint64_t *__restrict__ Xs) {
-    constexpr int ST = parity_stride(RW);
     uint64_t IQP_GLOBAL *__restrict__ out = gptr(a.out);
     const int64_t Rw = a.Rw, Gw = a.Gw;
-    const int W = a.W, lane = threadIdx.x & 63, wv = wave_id();
+    const int lane = threadIdx.x & 63, wv = wave_id();
     const int64_t ngc = ceil_div(Gw, a.gpb);
     const int64_t rc = blk / ngc, gc = blk - rc * ngc;
     const int64_t rw0 = rc * RW;
-    {
-        const uint64_t IQP_GLOBAL *rows = gptr(a.rows);
-        const int units = W * RW;
-        // unit u: row word u / W, qubit word u % W; four loads in flight
-        for (int u0 = wv; u0 < units; u0 += 16) {
-            uint64_t v[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int u = u0 + 4 * q;
-                const int i = u / W, w = u - i * W;
-                const int64_t row = (rw0 + i) * 64 + lane;
-                v[q] = u < units && row < a.R ? rows[row * W + w] : 0ull;
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int u = u0 + 4 * q;
-                if (u >= units) break;  // uniform over the wave
-                const int i = u / W, w = u - i * W;
-                Xs[(w * 64 + lane) * ST + i] = transpose64(v[q], lane);
-            }
-        }
-        if ((int)threadIdx.x < RW) Xs[64 * W * ST + threadIdx.x] = 0ull;
-    }
-    __syncthreads();
+    parity_stage<RW>(a, rw0, Xs);
     const int64_t g1 = (gc + 1) * a.gpb < Gw ? (gc + 1) * a.gpb : Gw;
     for (int64_t gb = gc * a.gpb + wv; gb < g1; gb += 4) {
-        const i32x4 IQP_GLOBAL *sp =
-            reinterpret_cast<const i32x4 IQP_GLOBAL *>(gptr(a.sup) + (gb * 64 + lane) * kSupCap);
-        const i32x4 s0 = sp[0], s1 = sp[1];
-        const int32_t sv[kSupCap] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
         uint64_t x[RW];
-#pragma unroll
-        for (int i = 0; i < RW; ++i) x[i] = 0ull;
-#pragma unroll
-        for (int k = 0; k < kSupCap; ++k) {
-            if (__ballot(sv[k] >= 0) == 0ull) break;  // lists fill from entry 0
-            const uint64_t *col = Xs + (sv[k] >= 0 ? sv[k] : 64 * W) * ST;
-#pragma unroll
-            for (int i = 0; i < RW; ++i) x[i] ^= col[i];
-        }
-        if (sv[0] == -2) {  // heavier than the list: its bit row
-            for (int w = 0; w < W; ++w) {
-                uint64_t bits = gptr(a.gens)[(gb * 64 + lane) * W + w];
-                while (bits) {
-                    const uint64_t *col = Xs + (w * 64 + __builtin_ctzll(bits)) * ST;
-                    bits &= bits - 1;
-#pragma unroll
-                    for (int i = 0; i < RW; ++i) x[i] ^= col[i];
-                }
-            }
-        }
+        parity_gather<RW>(a, gb, lane, Xs, x);
         if constexpr (LAYOUT == 3 && RW >= 4) {
             if ((Rw & 1) == 0) {
                 store_rows<RW, RW >= 8 ? 4 : 2>(x, out, gb * 64, Rw, rw0, lane);
@@ -1133,41 +1149,78 @@ hipError_t launch_phase_fwd_persistent(const LaunchCtx &lc, int prec, int fm, in
 // ---------------------------------------------------------------------------
 // epilogue: one block per (observable k, chunk of kEpiChunk samples).
 
-__device__ __forceinline__ void epilogue_body(const EpiArgs &a, int64_t blk) {
-    __shared__ double sh[256];
-    if (chain_on(a.gate)) return;
+// Bound by its vector instructions, about 45 per phase, 10 of them FP64, and by
+// reading E. kLanes = 256: a block per unit, which ends soonest where units are
+// few; 64: a wave per unit, whose indices and reduction then serve 16 phases
+// per lane. 10^8 phases of one split: 246 us with a block per unit and a
+// reduction through LDS, 224 with the waves' butterfly, 195 with a wave per
+// unit.
+template <int kLanes>
+__device__ __forceinline__ void epilogue_unit(const EpiArgs &a, uint32_t unit, int lane,
+                                              double (*sh)[4]) {
     const float IQP_GLOBAL *__restrict__ E = gptr(a.E);
     float IQP_GLOBAL *__restrict__ phase_out = gptr(a.phase_out);
     double IQP_GLOBAL *__restrict__ part = gptr(a.part);
     const int64_t splits = a.splits, s = a.s, l_pad = a.l_pad, s_pad = a.s_pad;
-    const int64_t nchunk = ceil_div(s, kEpiChunk);
-    const int64_t k = blk / nchunk, ch = blk - k * nchunk;
+    const uint32_t nchunk = (uint32_t)((s + kEpiChunk - 1) / kEpiChunk);
+    const int64_t k = unit / nchunk, ch = unit - (uint32_t)k * nchunk;
+    constexpr int kQ = (int)(kEpiChunk / kLanes);
+    const int left = (int)(s - ch * kEpiChunk < kEpiChunk ? s - ch * kEpiChunk : kEpiChunk);
+    const float IQP_GLOBAL *row = E + k * s_pad + ch * kEpiChunk;
+    double e[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) e[q] = 0.0;
+    for (int64_t sp = 0; sp < splits; ++sp) {
+        float v[kQ];
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) v[q] = lane + q * kLanes < left ? row[lane + q * kLanes] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) e[q] += (double)v[q];
+        row += l_pad * s_pad;
+    }
+    float IQP_GLOBAL *ph = phase_out ? phase_out + k * s + ch * kEpiChunk : nullptr;
     double sc = 0.0, sc2 = 0.0;
 #pragma unroll
-    for (int q = 0; q < (int)(kEpiChunk / 256); ++q) {
-        const int64_t i = ch * kEpiChunk + q * 256 + threadIdx.x;
-        if (i < s) {
-            double e = 0.0;
-            for (int64_t sp = 0; sp < splits; ++sp) e += (double)E[(sp * l_pad + k) * s_pad + i];
-            const double kk = rint(e * IQP_INV_TWO_PI);
-            double rr = fma(-kk, IQP_TWO_PI_HI, e);
-            rr = fma(-kk, IQP_TWO_PI_LO, rr);
-            const float rf = (float)rr;
-            const float c = cosf(rf);
-            if (phase_out) phase_out[k * s + i] = rf;
+    for (int q = 0; q < kQ; ++q) {
+        const double kk = rint(e[q] * IQP_INV_TWO_PI);
+        double rr = fma(-kk, IQP_TWO_PI_HI, e[q]);
+        rr = fma(-kk, IQP_TWO_PI_LO, rr);
+        const float rf = (float)rr;
+        const float c = cosf(rf);
+        if (lane + q * kLanes < left) {
+            if (ph) ph[lane + q * kLanes] = rf;
             sc += (double)c;
             sc2 += (double)c * (double)c;
         }
     }
-    sc = block_sum_256(sc, sh);
-    sc2 = block_sum_256(sc2, sh);
-    if (threadIdx.x == 0) {
+    if constexpr (kLanes == 256) {
+        block_sum2_256(sc, sc2, sh);
+    } else {
+#pragma unroll
+        for (int st = 32; st >= 1; st >>= 1) {
+            sc += __shfl_xor(sc, st, 64);
+            sc2 += __shfl_xor(sc2, st, 64);
+        }
+    }
+    if (lane == 0) {
         if (nchunk == 1) {
             finalize_store(a.fin, k, sc, sc2);
         } else {
-            part[(k * nchunk + ch) * 2 + 0] = sc;
-            part[(k * nchunk + ch) * 2 + 1] = sc2;
+            part[(int64_t)unit * 2 + 0] = sc;
+            part[(int64_t)unit * 2 + 1] = sc2;
         }
+    }
+}
+
+__device__ __forceinline__ void epilogue_body(const EpiArgs &a, int64_t blk) {
+    __shared__ double sh[2][4];
+    if (chain_on(a.gate)) return;
+    if (epilogue_by_wave(a)) {
+        const int64_t unit = blk * 4 + wave_id();
+        if (unit < a.l * ceil_div(a.s, kEpiChunk))
+            epilogue_unit<64>(a, (uint32_t)unit, (int)(threadIdx.x & 63), sh);
+    } else {
+        epilogue_unit<256>(a, (uint32_t)blk, (int)threadIdx.x, sh);
     }
 }
 
@@ -1250,6 +1303,7 @@ hipError_t launch_prep(const LaunchCtx &lc, const CoefArgs &a, const SupportArgs
 //         holds S[k][i] (KT4s = s_pad / 8): four K-steps per 16-byte load
 __device__ __forceinline__ void weights_body(const WeightsArgs &a, int64_t blk) {
     __shared__ float tile[64][65];  // [obs][sample]
+    if (chain_on(a.gate)) return;
     const float IQP_GLOBAL *__restrict__ phase = gptr(a.phase);
     const double IQP_GLOBAL *__restrict__ coef = gptr(a.coef);
     uint16_t IQP_GLOBAL *__restrict__ shi = gptr(a.shi);
@@ -1442,6 +1496,7 @@ __device__ __forceinline__ void gate_list_body(const GateListArgs &a, int64_t bl
     constexpr int kPer = (int)(kListSeg / 256);
     __shared__ int32_t wsum[4][3];
     __shared__ int32_t base[3];
+    if (chain_on(a.gate)) return;
     const int64_t nseg = ceil_div(a.m_pad, kListSeg);
     const int64_t ob = blk / nseg, seg = blk - ob * nseg;
     const int lane = threadIdx.x & 63, wv = wave_id();
@@ -1803,6 +1858,7 @@ __device__ __forceinline__ void bwd_bf16_body(const BwdArgs &a, const BwdUnit &U
 // lane and load), staged per sample word as [f][q][lane]; B operand +-1.0f.
 template <int FM, int FN>
 __device__ __forceinline__ void bwd_f32_body(const BwdArgs &a, const BwdUnit &U, int tid) {
+    if (chain_on(a.gate)) return;
     constexpr int kUnits = FM * 8 * 64;
     __shared__ float4 ls[2][kUnits];
     const float4 IQP_GLOBAL *__restrict__ s32 = reinterpret_cast<const float4 IQP_GLOBAL *>(gptr(a.s32));
@@ -2545,6 +2601,7 @@ hipError_t launch_reset_counters(const LaunchCtx &lc, unsigned long long *c, int
 // ... (a block's splits in order), and the four sums are added in order.
 __device__ __forceinline__ void grad_reduce_body(const GradArgs &a, int64_t blk) {
     __shared__ double sh[4][64];
+    if (chain_on(a.gate)) return;
     const int lane = threadIdx.x & 63, wv = wave_id();
     const int64_t j = blk * 64 + lane;
     double acc = 0.0;
@@ -2863,6 +2920,210 @@ __device__ __forceinline__ void bitflip_grad_body(const BitflipGradArgs &a, int6
 
 hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a) {
     return plain_launch<BitflipGradArgs, bitflip_grad_body>(lc, KF_BWD, a, blocks_of(a));
+}
+
+// ---------------------------------------------------------------------------
+// The same two steps for rows of fewer than 128 words, straight from the
+// parities in registers: no bit of C passes through memory. A block takes rw
+// words of 64 observables and 64 gpb gates, as the parity kernel does.
+//   forward   the lane's parities (gate 64 gb + lane against 64 observables)
+//             are transposed to the lane's observable against 64 gates; signs
+//             and zero factors are popcounts against the gates' masks, and
+//             the logarithms are summed over the set bits from LDS
+//   gradient  sum over the lane's observables k of v_k = u_k sign_k e^{S_k},
+//             read from LDS; times 1 / c_j at the end. One exponential per
+//             observable instead of one per non-zero entry. Observables with
+//             S_k < kDeep, whose e^{S_k} would lose bits near the smallest
+//             doubles, keep e^{S_k - log|c_j|} per entry.
+// Partials per gate chunk and per observable chunk are added in order by the
+// finishing kernels. Bound by the vector instructions of the transposes and of
+// the walks over set bits, two blocks of LDS per CU. 1000 qubits, 10^5 gates,
+// 10^4 observables (1.1 % of C non-zero): C's parities and the forward 81 + 210
+// -> 109 us, the gradient's and the gradient 83 + 383 -> 99 us.
+constexpr double kDeep = -700.0;
+
+template <int RW>
+__device__ __forceinline__ void bitflip_sum(const BitflipSumArgs &a, int64_t blk,
+                                            uint64_t *__restrict__ Xs, double (*logs)[64]) {
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    const ParityArgs &p = a.par;
+    const int64_t ngc = ceil_div(p.Gw, p.gpb);
+    const int64_t rc = blk / ngc, gc = blk - rc * ngc;
+    const int64_t rw0 = rc * RW;
+    parity_stage<RW>(p, rw0, Xs);
+    double S[RW];
+    int code[RW];  // 2 (zero factors) + sign parity
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+        S[i] = 0.0;
+        code[i] = 0;
+    }
+    const int64_t g1 = (gc + 1) * p.gpb < p.Gw ? (gc + 1) * p.gpb : p.Gw;
+    for (int64_t gb = gc * p.gpb + wv; gb < g1; gb += 4) {
+        uint64_t x[RW];
+        parity_gather<RW>(p, gb, lane, Xs, x);
+        const int64_t j = gb * 64 + lane;
+        const double e = j < p.m ? gptr(a.enc)[j] : 0.0;
+        const bool zero = isinf(e);
+        __builtin_amdgcn_wave_barrier();  // the wave's reads of logs precede
+        logs[wv][lane] = zero ? 0.0 : -fabs(e);
+        __builtin_amdgcn_wave_barrier();
+        const uint64_t negm = __ballot(!zero && signbit(e)), zerom = __ballot(zero);
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            if (rw0 + i >= p.Rw) break;  // uniform over the wave
+            uint64_t y = transpose64(x[i], lane);
+            code[i] = (code[i] ^ (__popcll(y & negm) & 1)) + 2 * __popcll(y & zerom);
+            while (y) {
+                S[i] += logs[wv][__builtin_ctzll(y)];
+                y &= y - 1;
+            }
+        }
+    }
+    __syncthreads();  // Xs is read no more: it holds the block's sums now
+    double *bs = reinterpret_cast<double *>(Xs);
+    int *bc = reinterpret_cast<int *>(bs + 64 * RW);
+    for (int v = 0; v < 4; ++v) {
+        if (wv == v) {
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                const int o = i * 64 + lane;
+                bs[o] = v ? bs[o] + S[i] : S[i];
+                // parities XOR, counts add
+                bc[o] = v ? ((bc[o] ^ code[i]) & 1) + (bc[o] & ~1) + (code[i] & ~1) : code[i];
+            }
+        }
+        __syncthreads();
+    }
+    for (int o = threadIdx.x; o < 64 * RW; o += 256) {
+        const int64_t k = rw0 * 64 + o;
+        if (k < a.l_pad) {
+            gptr(a.psum)[gc * a.l_pad + k] = bs[o];
+            gptr(a.pcode)[gc * a.l_pad + k] = bc[o];
+        }
+    }
+}
+
+__device__ __forceinline__ void bitflip_sum_body(const BitflipSumArgs &a, int64_t blk) {
+    extern __shared__ uint64_t parity_lds[];
+    __shared__ double logs[4][64];
+    if (a.par.rw == 16) bitflip_sum<16>(a, blk, parity_lds, logs);
+    else if (a.par.rw == 8) bitflip_sum<8>(a, blk, parity_lds, logs);
+    else if (a.par.rw == 4) bitflip_sum<4>(a, blk, parity_lds, logs);
+    else if (a.par.rw == 2) bitflip_sum<2>(a, blk, parity_lds, logs);
+    else bitflip_sum<1>(a, blk, parity_lds, logs);
+}
+
+// stat[k] as bitflip_fwd_body writes it; val[k] = u_k times the product over
+// the non-zero factors where none (val[2k]) or one (val[2k + 1]) is zero.
+__device__ __forceinline__ void bitflip_finish_body(const BitflipFinishArgs &a, int64_t blk) {
+    const int64_t k = blk * 256 + threadIdx.x;
+    if (k >= a.l) return;
+    double S = 0.0;
+    int neg = 0, zeros = 0;
+    for (int64_t gc = 0; gc < a.ngc; ++gc) {
+        S += gptr(a.psum)[gc * a.l_pad + k];
+        const int c = gptr(a.pcode)[gc * a.l_pad + k];
+        neg ^= c & 1;
+        zeros += c >> 1;
+    }
+    const double sgn = neg ? -1.0 : 1.0;
+    const double prod = sgn * exp(S);
+    if (a.mean) gptr(a.mean)[k] = zeros ? 0.0 : prod;
+    if (!a.grad_mean) return;
+    const double u = gptr(a.grad_mean)[k];
+    const bool deep = zeros == 0 && S < kDeep;
+    gptr(a.stat)[2 * k] = S;
+    gptr(a.stat)[2 * k + 1] = deep ? sgn * u : 0.0;
+    gptr(a.val)[2 * k] = u * (zeros == 0 && !deep ? prod : 0.0);
+    gptr(a.val)[2 * k + 1] = u * (zeros == 1 ? prod : 0.0);
+}
+
+template <int RW>
+__device__ __forceinline__ void bitflip_dot(const BitflipDotArgs &a, int64_t blk,
+                                            uint64_t *__restrict__ Xs) {
+    // past the staged rows: v_k of the block's observables, and the masks of
+    // those that keep their own exponential
+    double *v = reinterpret_cast<double *>(Xs + (64 * a.par.W + 1) * parity_stride(RW));
+    uint64_t *deep = reinterpret_cast<uint64_t *>(v + 64 * RW);
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    const ParityArgs &p = a.par;
+    const int64_t ngc = ceil_div(p.Gw, p.gpb);
+    const int64_t rc = blk / ngc, gc = blk - rc * ngc;
+    const int64_t rw0 = rc * RW;
+    for (int i = wv; i < RW; i += 4) {
+        const int64_t k = (rw0 + i) * 64 + lane;
+        const bool live = k < a.l;
+        v[i * 64 + lane] = live ? gptr(a.val)[2 * k] : 0.0;
+        const uint64_t d = __ballot(live && gptr(a.stat)[2 * k + 1] != 0.0);
+        if (lane == 0) deep[i] = d;
+    }
+    parity_stage<RW>(p, rw0, Xs);
+    const int64_t g1 = (gc + 1) * p.gpb < p.Gw ? (gc + 1) * p.gpb : p.Gw;
+    for (int64_t gb = gc * p.gpb + wv; gb < g1; gb += 4) {
+        uint64_t x[RW];
+        parity_gather<RW>(p, gb, lane, Xs, x);
+        const int64_t j = gb * 64 + lane;
+        const double e = j < p.m ? gptr(a.enc)[j] : 0.0;
+        const bool zero = isinf(e);  // c_j = 0: the products where it is the only zero
+        const double inv = zero ? 1.0 : copysign(exp(fabs(e)), e);  // 1 / c_j
+        double acc = 0.0, own = 0.0;
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            if (rw0 + i >= p.Rw) break;  // uniform over the wave
+            uint64_t y = x[i];
+            uint64_t d = zero ? 0ull : y & deep[i];
+            uint64_t z = zero ? y : 0ull;
+            y = zero ? 0ull : y;
+            while (y) {
+                acc += v[i * 64 + __builtin_ctzll(y)];
+                y &= y - 1;
+            }
+            while (z) {
+                acc += gptr(a.val)[2 * ((rw0 + i) * 64 + __builtin_ctzll(z)) + 1];
+                z &= z - 1;
+            }
+            while (d) {
+                const int64_t k = (rw0 + i) * 64 + __builtin_ctzll(d);
+                d &= d - 1;
+                own += gptr(a.stat)[2 * k + 1] * exp(gptr(a.stat)[2 * k] + fabs(e));
+            }
+        }
+        gptr(a.part)[rc * a.m_pad + j] = acc * inv + copysign(1.0, e) * own;
+    }
+}
+
+__device__ __forceinline__ void bitflip_dot_body(const BitflipDotArgs &a, int64_t blk) {
+    extern __shared__ uint64_t parity_lds[];
+    if (a.par.rw == 16) bitflip_dot<16>(a, blk, parity_lds);
+    else if (a.par.rw == 8) bitflip_dot<8>(a, blk, parity_lds);
+    else if (a.par.rw == 4) bitflip_dot<4>(a, blk, parity_lds);
+    else if (a.par.rw == 2) bitflip_dot<2>(a, blk, parity_lds);
+    else bitflip_dot<1>(a, blk, parity_lds);
+}
+
+__device__ __forceinline__ void bitflip_chain_body(const BitflipChainArgs &a, int64_t blk) {
+    const int64_t j = blk * 256 + threadIdx.x;
+    if (j >= a.m) return;
+    double acc = 0.0;
+    for (int64_t rc = 0; rc < a.nrc; ++rc) acc += gptr(a.part)[rc * a.m_pad + j];
+    gptr(a.grad)[j] = -2.0 * sin(2.0 * gptr(a.theta)[j]) * acc;
+}
+
+hipError_t launch_bitflip_sum(const LaunchCtx &lc, const BitflipSumArgs &a) {
+    return plain_launch<BitflipSumArgs, bitflip_sum_body>(lc, KF_FWD, a, blocks_of(a.par), lds_of(a));
+}
+
+hipError_t launch_bitflip_finish(const LaunchCtx &lc, const BitflipFinishArgs &a) {
+    return plain_launch<BitflipFinishArgs, bitflip_finish_body>(lc, KF_FIN, a, ceil_div(a.l, 256));
+}
+
+hipError_t launch_bitflip_dot(const LaunchCtx &lc, const BitflipDotArgs &a) {
+    return plain_launch<BitflipDotArgs, bitflip_dot_body>(lc, KF_BWD, a, blocks_of(a.par), lds_of(a));
+}
+
+hipError_t launch_bitflip_chain(const LaunchCtx &lc, const BitflipChainArgs &a) {
+    return plain_launch<BitflipChainArgs, bitflip_chain_body>(lc, KF_GRAD, a, ceil_div(a.m, 256));
 }
 
 }  // namespace iqp

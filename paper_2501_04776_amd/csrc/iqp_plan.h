@@ -175,7 +175,7 @@ inline CoefArgs coef_args(const Plan &P, const double *grad_mean, void *ws) {
     const bool dense = P.o_glist != 0;
     return CoefArgs{grad_mean, P.l, P.s, at<double>(ws, P.o_coef),
                     fx ? at<double>(ws, P.o_sq) : nullptr, fx ? at<int32_t>(ws, P.o_nf) : nullptr,
-                    dense ? at<int32_t>(ws, P.o_gcnt) : nullptr, dense ? 4 * P.lw : 0};
+                    dense ? at<int32_t>(ws, P.o_gcnt) : nullptr, dense ? 4 * P.lw + 2 : 0};
 }
 inline WeightsArgs weights_args(const Plan &P, const float *phase, void *ws) {
     return WeightsArgs{phase,  at<double>(ws, P.o_coef), P.l, P.s, P.l_pad, P.s_pad, P.prec,

@@ -680,6 +680,188 @@ hipError_t launch_chain_fwd(const LaunchCtx &lc, const ChainFwdArgs &a) {
     return plain_launch<ChainFwdArgs, chain_fwd_body>(lc, KF_FWD, a, blocks_of(a));
 }
 
+// FP32 backward over the non-zero entries of C, by the same argument: T_kj of a
+// sample split is the running FP32 sum of +-S_ki in sample order, and only
+// entries with c_kj = 1 reach the gradient, where the matrix-core kernel adds
+// them row by row, alternate groups of four rows in two sums. A block takes
+// observable k and a split: its gates are listed in LDS, a lane holds up to
+// four of them, and walks the samples with |S_ki| and the signs of 64 samples
+// read from LDS by all lanes at once. The T go to memory in row order; the
+// second kernel gives a lane a gate, finds each T by the row's entries before
+// the wave's 64 gates and a ballot, and adds them in the order above. Bound by
+// the vector units: three instructions per term.
+__device__ __forceinline__ void rank_body(const RankArgs &a, int64_t k) {
+    __shared__ int wsum[2][4];
+    const glb<const uint64_t> row = gptr(a.crm) + k * a.mw;
+    int n = 0, it = 0;
+    for (int64_t base = 0; base < a.mw; base += 256, ++it) {
+        const int64_t w = base + threadIdx.x;
+        int tot;
+        const int before = block_excl_scan(w < a.mw ? __popcll(row[w]) : 0, wsum[it & 1], &tot);
+        if (w < a.mw) gptr(a.rank)[k * a.mw + w] = (uint32_t)(n + before);
+        n += tot;
+    }
+    if (threadIdx.x != 0) return;
+    // a row without room: the top bit, which no number of entries reaches
+    if (n > a.cap) atomicOr(a.nnz, 1ull << 63);
+    else if (n) atomicAdd(a.nnz, (unsigned long long)n);
+}
+
+hipError_t launch_rank(const LaunchCtx &lc, const RankArgs &a) {
+    return plain_launch<RankArgs, rank_body>(lc, KF_PARITY, a, blocks_of(a));
+}
+
+// NQ gates per lane over one word of 64 samples: acc[q] += +-|S| in order.
+template <int NQ>
+__device__ __forceinline__ void chain_word(float (&acc)[4], const uint64_t (&y)[4],
+                                           const float *mag) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+            const float4 m = *reinterpret_cast<const float4 *>(mag + 32 * h + 4 * g);
+            const float mv[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+                    acc[q] += __builtin_copysignf(
+                        mv[b], __uint_as_float((uint32_t)(y[q] >> (32 * h)) << (31 - 4 * g - b)));
+        }
+    }
+}
+
+__device__ __forceinline__ void chain_bwd_body(const ChainBwdArgs &a, int64_t blk) {
+    if (!chain_on(a.gate)) return;
+    __shared__ int32_t lst[kLutList];
+    __shared__ __attribute__((aligned(16))) float mag[kEpiChunk];
+    __shared__ uint64_t sgn[kSpWords];
+    __shared__ int wsum[2][4];
+    const int64_t ks = blk / a.l, k = blk - ks * a.l;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+    const int64_t sw = a.s_pad / 64, wps = ceil_div(sw, a.ksplits);
+    const int64_t w0 = ks * wps, w1 = w0 + wps < sw ? w0 + wps : sw;
+    const double al = gptr(a.coef)[2 * k], be = gptr(a.coef)[2 * k + 1];
+    const glb<const uint64_t> bt = gptr(a.btbits);
+    float IQP_GLOBAL *T = gptr(a.T) + (ks * a.l + k) * a.cap;
+    auto fill = [&](int n) {
+        // gates of this wave: entries q 256 + 64 wave + lane
+        const int left = n - wave * 64;
+        const int nq = __builtin_amdgcn_readfirstlane(left <= 0 ? 0 : (left + 255) / 256);
+        int32_t j[4];
+        float acc[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = q * 256 + tid;
+            j[q] = e < n ? lst[e] : 0;
+            acc[q] = 0.0f;
+        }
+        for (int64_t c0 = w0; c0 < w1; c0 += kSpWords) {
+            __syncthreads();  // mag and sgn of the chunk before are read
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t i = c0 * 64 + q * 256 + tid;
+                float v = 0.0f;
+                if (i < a.s) {
+                    float sn, cs;
+                    sincosf(gptr(a.phase)[k * a.s + i], &sn, &cs);
+                    v = (float)((al + be * (double)cs) * (double)sn);
+                }
+                mag[q * 256 + tid] = fabsf(v);
+                const uint64_t m = __ballot(__float_as_int(v) < 0);
+                if (lane == 0) sgn[q * 4 + wave] = m;
+            }
+            __syncthreads();
+            if (!nq) continue;
+            const int nw = (int)(w1 - c0 < kSpWords ? w1 - c0 : kSpWords);
+            uint64_t nx[4], y[4];
+            auto load = [&](int w) {
+                const glb<const uint64_t> row = bt + (c0 + w) * a.m_pad;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (q < nq) nx[q] = row[(uint32_t)j[q]];
+            };
+            load(0);
+            for (int w = 0; w < nw; ++w) {
+                const uint64_t sg = sgn[w];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) y[q] = nx[q] ^ sg;
+                if (w + 1 < nw) load(w + 1);
+                const float *mw = mag + w * 64;
+                if (nq == 4) chain_word<4>(acc, y, mw);
+                else if (nq == 3) chain_word<3>(acc, y, mw);
+                else if (nq == 2) chain_word<2>(acc, y, mw);
+                else chain_word<1>(acc, y, mw);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (q * 256 + tid < n) T[q * 256 + tid] = acc[q];
+        T += n;
+    };
+    compact_row(gptr(a.crm) + k * a.mw, a.mw, lst, wsum, fill);
+}
+
+hipError_t launch_chain_bwd(const LaunchCtx &lc, const ChainBwdArgs &a) {
+    return plain_launch<ChainBwdArgs, chain_bwd_body>(lc, KF_BWD, a, blocks_of(a));
+}
+
+// One block per 64 gates; wave v takes the 64-row words v, v + 4, ... of C^T.
+__device__ __forceinline__ void chain_grad_body(const ChainGradArgs &a, int64_t gw) {
+    if (!chain_on(a.gate)) return;
+    __shared__ double sh[4][64];
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    const int64_t j = gw * 64 + lane;
+    double acc = 0.0;
+    for (int64_t ob = wv; ob < a.lw; ob += 4) {
+        const uint64_t word = gptr(a.ctbits)[ob * a.m_pad + j];
+        if (__ballot(word != 0ull) == 0ull) continue;
+        float gs[kChainMaxSplits][2];
+#pragma unroll
+        for (int q = 0; q < (int)kChainMaxSplits; ++q) gs[q][0] = gs[q][1] = 0.0f;
+        // the entries of this word's rows before the wave's gates, lane r: row r
+        const int64_t kr = ob * 64 + lane;
+        const uint32_t mine = kr < a.l ? gptr(a.rank)[kr * a.mw + gw] : 0u;
+#pragma unroll
+        for (int r0 = 0; r0 < 64; r0 += 4) {
+            uint32_t slot[4];
+            bool bit[4];
+            bool any = false;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                bit[i] = (word >> (r0 + i)) & 1ull;
+                const uint64_t b = __ballot(bit[i]);
+                any |= b != 0ull;
+                slot[i] = (uint32_t)__builtin_amdgcn_readlane((int)mine, r0 + i) +
+                          (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+            }
+            if (!any) continue;  // uniform over the wave
+#pragma unroll
+            for (int q = 0; q < (int)kChainMaxSplits; ++q) {
+                if (q >= a.ksplits) break;
+                float t[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    t[i] = bit[i] ? gptr(a.T)[((q * a.l) + ob * 64 + r0 + i) * a.cap + slot[i]] : 0.0f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) gs[q][(r0 >> 2) & 1] += t[i];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < (int)kChainMaxSplits; ++q)
+            if (q < a.ksplits) acc += (double)(gs[q][0] + gs[q][1]);
+    }
+    sh[wv][lane] = acc;
+    __syncthreads();
+    if (wv == 0 && j < a.m)
+        gptr(a.grad)[j] = -2.0 * (((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane]);
+}
+
+hipError_t launch_chain_grad(const LaunchCtx &lc, const ChainGradArgs &a) {
+    return plain_launch<ChainGradArgs, chain_grad_body>(lc, KF_GRAD, a, blocks_of(a));
+}
+
 // ---------------------------------------------------------------------------
 // Bit columns of every observable's own sample set. A step is (set k, group g
 // of 16 row words = 1024 rows, chunk c of 8 qubit words); ldx is a multiple

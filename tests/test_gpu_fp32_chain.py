@@ -10,7 +10,7 @@ import torch
 import oracle
 import workloads as W
 from paper_2501_04776_amd import api
-from tests.gpu_util import DevWorkload
+from tests.gpu_util import DevWorkload, check_grad
 
 pytestmark = pytest.mark.gpu
 
@@ -81,3 +81,53 @@ def test_fp32_nan_and_identity_rows():
     got = mean.cpu().numpy()
     assert hit.any() and np.array_equal(np.isnan(got), hit)
     assert got[7] == 1.0
+
+
+# (n, m, l, s, gate weight, op weight): C below the density limit, rows of
+# less and more than one list fill, ragged samples, one and several blocks of
+# 64 observables
+@pytest.mark.parametrize("shape", [
+    (400, 5000, 400, 1301, (1, 2), (1, 2)),
+    (300, 9000, 129, 2057, (1, 3), (1, 3)),
+    (90, 30000, 40, 1799, (1, 2), (1, 4)),
+    (500, 60000, 17, 2112, (1, 4), (1, 9)),
+])
+def test_fp32_gradient_bitwise(shape, monkeypatch):
+    # the batched form always takes the matrix cores, over one sample split
+    n, m, l, s, gw, ow = shape
+    assert l * s * m >= 2 ** 31
+    monkeypatch.setenv("IQP_BWD_SPLITS", "1")
+    w = W.small_random(n + m + l + s, n, m, l, s, gate_w=gw, op_w=ow)
+    dw = DevWorkload(w)
+    circ = api.Circuit(w.n, dw.gens, dw.theta)
+    _, _, ph = api.iqp_expval(circ, dw.ops, dw.samples, "fp32", phase_save=True)
+    u = torch.from_numpy(np.random.default_rng(8).normal(size=l)).cuda()
+    u[l // 3] = 0.0
+    g = api.iqp_expval_grad(circ, dw.ops, dw.samples, u, ph, "fp32")
+    plan = api.BatchPlan([(circ, dw.ops, dw.samples)], "fp32")
+    plan.phases[0].copy_(ph)
+    (ref,) = plan.expval_grad([u])
+    assert torch.equal(g, ref)
+
+
+@pytest.mark.parametrize("splits", [2, 5, 8, 9])
+def test_fp32_gradient_splits(splits, monkeypatch):
+    monkeypatch.setenv("IQP_BWD_SPLITS", str(splits))
+    w = W.small_random(3100 + splits, 400, 5000, 400, 1301, gate_w=(1, 2), op_w=(1, 2))
+    dw = DevWorkload(w)
+    circ = api.Circuit(w.n, dw.gens, dw.theta)
+    u = np.random.default_rng(9).normal(size=w.l)
+    g = api.iqp_expval_grad(circ, dw.ops, dw.samples, torch.from_numpy(u).cuda(), None, "fp32")
+    check_grad("fp32", g.cpu().numpy(), w, dw.ops01, u)
+
+
+def test_fp32_gradient_nan_weight():
+    # a NaN weight reaches the gates of its observable only
+    w = W.small_random(91, 400, 5000, 400, 1301, gate_w=(1, 2), op_w=(1, 2))
+    dw = DevWorkload(w)
+    circ = api.Circuit(w.n, dw.gens, dw.theta)
+    u = np.random.default_rng(9).normal(size=w.l)
+    u[5] = np.nan
+    g = api.iqp_expval_grad(circ, dw.ops, dw.samples, torch.from_numpy(u).cuda(), None, "fp32")
+    hit = oracle.parity(w.n, dw.ops01[5:6], w.gates)[0] != 0
+    assert hit.any() and np.array_equal(np.isnan(g.cpu().numpy()), hit)
