@@ -470,15 +470,16 @@ static int check_ws(const Plan &P, void *ws, size_t ws_bytes) {
 
 
 // The sparse kernels' sample parities: B^T row-major, shared by all observables.
-static SampleParity shared_parity(const Plan &P, void *ws) {
+static SampleParity shared_parity(const Plan &P, const uint64_t *ops, void *ws) {
     return SampleParity{at<uint64_t>(ws, P.o_btbits), nullptr, P.s_pad / 64, 0, nullptr, nullptr,
-                        (int)P.W};
+                        (int)P.W, ops};
 }
 
 // Independent estimates: the bit columns of each observable's own samples.
-static SampleParity indep_parity(const Plan &P, const iqp_circuit *c, void *ws) {
+static SampleParity indep_parity(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
+                                 void *ws) {
     return SampleParity{nullptr,     at<uint64_t>(ws, P.o_xz), P.ldz,   64 * P.W * P.ldz,
-                        at<int32_t>(ws, P.o_sup), c->gens,     (int)P.W};
+                        at<int32_t>(ws, P.o_sup), c->gens,     (int)P.W, ops};
 }
 
 // C row-major and the per-observable sample bit columns of the independent
@@ -583,7 +584,7 @@ static int run_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
         int st = run_sparse_parities(P, c, ops, samples, ws, lc);
         if (st) return st;
         IQP_TRY(launch_sparse_fwd(lc, SparseFwdArgs{at<uint64_t>(ws, P.o_cbits), P.mw,
-                                                    at<float>(ws, P.o_t32), shared_parity(P, ws),
+                                                    at<float>(ws, P.o_t32), shared_parity(P, ops, ws),
                                                     P.l, P.s, phase_out,
                                                     at<double>(ws, P.o_part), fin}),
                 "sparse_fwd");
@@ -592,13 +593,36 @@ static int run_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
     }
     if (P.prec == IQP_FP32 && (double)P.l * (double)P.s * (double)P.m >= kChainTerms)
         return run_forward_fp32(P, c, ops, samples, ws, lc, phase_out, mean, se, rowsum);
-    IQP_TRY(launch_prep(lc, theta_args(P, c->theta, ws), support_args(P, c->gens, ws)),
-            "theta_prep, support");
-    IQP_TRY(launch_parity2(lc, IQP_BITS_TILED32, parity_c_args(P, c->gens, ops, ws),
-                           IQP_BITS_TILED32, parity_b_args(P, c->gens, samples, ws)),
+    ThetaArgs th = theta_args(P, c->theta, ws);
+    ParityArgs pc = parity_c_args(P, c->gens, ops, ws);
+    FwdArgs fa = fwd_args(P, ws, P.tc.splits);
+    EpiArgs ea = epi_args(P, ws, P.tc.splits, phase_out, fin);
+    // Operators drawn for a wide kernel bandwidth are mostly of weight 0, and
+    // their rows of the product are all zero: the MMD forward leaves them out
+    // from the size on where the product takes well over the extra launch
+    // (2^34 terms, 40 us). The row table lives in the row sums, which the last
+    // step writes.
+    const bool drop = P.mmd && P.prec != IQP_FP32 && pc.rw && P.nchunk > 1 &&
+                      (double)P.l * (double)P.s * (double)P.m >= 17179869184.0;
+    if (drop) {
+        int32_t *nrows = at<int32_t>(ws, P.o_rowsum), *pos = nrows + 2, *perm = pos + P.l;
+        th.nnz = reinterpret_cast<unsigned long long *>(nrows);
+        pc.perm = RowPerm{perm, pos, nrows};
+        fa.nrows = nrows;
+        ea.pos = pos;
+    }
+    IQP_TRY(launch_prep(lc, th, support_args(P, c->gens, ws)), "theta_prep, support");
+    if (drop)
+        IQP_TRY(launch_row_perm(lc, RowPermArgs{ops, P.l, (int)P.W,
+                                                const_cast<int32_t *>(pc.perm.perm),
+                                                const_cast<int32_t *>(pc.perm.pos),
+                                                const_cast<int32_t *>(pc.perm.nrows)}),
+                "row_perm");
+    IQP_TRY(launch_parity2(lc, IQP_BITS_TILED32, pc, IQP_BITS_TILED32,
+                           parity_b_args(P, c->gens, samples, ws)),
             "parity(C, B)");
-    IQP_TRY(launch_fwd(lc, P, fwd_args(P, ws, P.tc.splits)), "phase_fwd");
-    IQP_TRY(launch_epilogue(lc, epi_args(P, ws, P.tc.splits, phase_out, fin)), "phase_epilogue");
+    IQP_TRY(launch_fwd(lc, P, fa), "phase_fwd");
+    IQP_TRY(launch_epilogue(lc, ea), "phase_epilogue");
     IQP_TRY(launch_finalize(lc, fin), "finalize");
     return IQP_OK;
 }
@@ -620,7 +644,7 @@ static int run_backward(const Plan &P, const iqp_circuit *c, const uint64_t *ops
             if (st) return st;
         }
         IQP_TRY(launch_sparse_bwd(lc, SparseBwdArgs{at<uint64_t>(ws, P.o_cbits), P.mw,
-                                                    shared_parity(P, ws), P.l, P.s, P.m_pad,
+                                                    shared_parity(P, ops, ws), P.l, P.s, P.m_pad,
                                                     phase, at<double>(ws, P.o_coef), scale, acc}),
                 "sparse_bwd");
         IQP_TRY(launch_sparse_finish(lc, SparseFinishArgs{acc, scale, P.m, P.m_pad, grad_theta}),
@@ -831,7 +855,7 @@ static int run_indep_forward(const Plan &P, const iqp_circuit *c, const uint64_t
     if (st) return st;
     const FinArgs fin = fin_args(P, ws, mean, se, at<double>(ws, P.o_rowsum));
     IQP_TRY(launch_sparse_fwd(lc, SparseFwdArgs{at<uint64_t>(ws, P.o_cbits), P.mw,
-                                                at<float>(ws, P.o_t32), indep_parity(P, c, ws),
+                                                at<float>(ws, P.o_t32), indep_parity(P, c, ops, ws),
                                                 P.l, P.s, phase_out, at<double>(ws, P.o_part),
                                                 fin}),
             "sparse_fwd(indep)");
@@ -894,7 +918,7 @@ int iqp_expval_indep_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops, 
                                                     acc, scale}),
             "sparse_bound");
     IQP_TRY(launch_sparse_bwd(lc, SparseBwdArgs{at<uint64_t>(ws, P.o_cbits), P.mw,
-                                                indep_parity(P, c, ws), P.l, P.s, P.m_pad, phase,
+                                                indep_parity(P, c, ops, ws), P.l, P.s, P.m_pad, phase,
                                                 at<double>(ws, P.o_coef), scale, acc}),
             "sparse_bwd(indep)");
     IQP_TRY(launch_sparse_finish(lc, SparseFinishArgs{acc, scale, P.m, P.m_pad, grad_theta}),

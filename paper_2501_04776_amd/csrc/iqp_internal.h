@@ -71,6 +71,13 @@ struct ChainGate {
     unsigned long long limit = 0;
 };
 
+// Observables of weight 0 (most operators of a wide kernel bandwidth) leave the
+// dense forward: the others, in any order, are rows 0 .. *nrows - 1 of C and E;
+// perm[row] = observable, pos[observable] = row or -1. NULL: all rows, in order.
+struct RowPerm {
+    const int32_t *perm = nullptr, *pos = nullptr, *nrows = nullptr;
+};
+
 // ---- per-step arguments -----------------------------------------------------
 // Each step's kernel body takes one of these and a block (or work-unit)
 // index. A single-problem launch passes the struct as the kernel argument; a
@@ -106,6 +113,15 @@ inline int64_t blocks_of(const BitsliceArgs &a) { return ceil_div(a.ldx * a.W, 4
 // are written as weight 0): sup[j * kSupCap + k] = qubit of the k-th set bit
 // of generator j, -1 past its weight, and sup[j * kSupCap] = -2 for a
 // generator heavier than kSupCap.
+// Finds the observables of weight > 0 (RowPerm; *nrows must read 0).
+struct RowPermArgs {
+    const uint64_t *ops;
+    int64_t l;
+    int W;
+    int32_t *perm, *pos, *nrows;
+};
+inline int64_t blocks_of(const RowPermArgs &a) { return ceil_div(a.l, 256); }
+
 struct SupportArgs {
     const uint64_t *gens;
     int64_t m;
@@ -138,6 +154,7 @@ struct ParityArgs {
     uint64_t *out;
     int rw;
     int64_t gpb;
+    RowPerm perm = {};  // rows: the first *nrows of them, row i being perm[i]
     ChainGate gate = {};
     int when = 0;  // 1: only for the matrix cores, 2: only for the other way
 };
@@ -179,7 +196,8 @@ struct FwdArgs {
     const float *t32;
     int64_t m_pad, l_pad, s_pad, splits;
     float *E;
-    ChainGate gate = {};  // FP32 only
+    const int32_t *nrows = nullptr;  // rows that are there (RowPerm)
+    ChainGate gate = {};             // FP32 only
 };
 inline int64_t fwd_units(const FwdArgs &a, int fm, int fn) {
     return (a.l_pad / (32 * fm)) * ceil_div(a.s_pad / (32 * fn), 4) * a.splits;
@@ -199,6 +217,7 @@ struct EpiArgs {
     float *phase_out;
     double *part;
     FinArgs fin = {};
+    const int32_t *pos = nullptr;  // RowPerm
     ChainGate gate = {};
 };
 
@@ -459,6 +478,7 @@ struct SampleParity {
     const int32_t *sup;
     const uint64_t *gens;
     int W;
+    const uint64_t *ops;  // the observables (W words each)
 };
 
 // Sparse-C contraction (FP32 on the vector units): the phases summed over
@@ -523,6 +543,7 @@ hipError_t launch_prep(const LaunchCtx &lc, const ThetaArgs &a, const SupportArg
 hipError_t launch_prep(const LaunchCtx &lc, const CoefArgs &a, const SupportArgs &b);
 hipError_t launch_prep(const LaunchCtx &lc, const BitflipPrepArgs &a, const SupportArgs &b);
 hipError_t launch_support(const LaunchCtx &lc, const SupportArgs &a);
+hipError_t launch_row_perm(const LaunchCtx &lc, const RowPermArgs &a);
 // Parities in one layout, or of two row sets: (la, lb) one of (1, 1), (4, 4),
 // (0, 3), (1, 2).
 hipError_t launch_parity(const LaunchCtx &lc, int layout, const ParityArgs &a);

@@ -345,6 +345,8 @@ __device__ __forceinline__ void parity_stage(const ParityArgs &a, int64_t rw0,
                                              uint64_t *__restrict__ Xs) {
     constexpr int ST = parity_stride(RW);
     const uint64_t IQP_GLOBAL *rows = gptr(a.rows);
+    const int32_t IQP_GLOBAL *perm = gptr(a.perm.perm);
+    const int64_t R = perm ? gptr(a.perm.nrows)[0] : a.R;
     const int W = a.W, lane = threadIdx.x & 63, wv = wave_id();
     const int units = W * RW;
     // unit u: row word u / W, qubit word u % W; four loads in flight
@@ -355,7 +357,7 @@ __device__ __forceinline__ void parity_stage(const ParityArgs &a, int64_t rw0,
             const int u = u0 + 4 * q;
             const int i = u / W, w = u - i * W;
             const int64_t row = (rw0 + i) * 64 + lane;
-            v[q] = u < units && row < a.R ? rows[row * W + w] : 0ull;
+            v[q] = u < units && row < R ? rows[(perm ? perm[row] : row) * W + w] : 0ull;
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -454,6 +456,30 @@ __device__ __forceinline__ void parity_body(const ParityArgs &a, int64_t blk) {
     else if (a.rw == 4) parity_rows<LAYOUT, 4>(a, blk, parity_lds);
     else if (a.rw == 2) parity_rows<LAYOUT, 2>(a, blk, parity_lds);
     else parity_rows<LAYOUT, 1>(a, blk, parity_lds);
+}
+
+__device__ __forceinline__ void row_perm_body(const RowPermArgs &a, int64_t blk) {
+    __shared__ int wsum[4];
+    __shared__ int base;
+    const int64_t k = blk * 256 + threadIdx.x;
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    uint64_t any = 0ull;
+    if (k < a.l)
+        for (int w = 0; w < a.W; ++w) any |= gptr(a.ops)[k * a.W + w];
+    const uint64_t b = __ballot(any != 0ull);
+    if (lane == 0) wsum[wv] = __popcll(b);
+    __syncthreads();
+    if (threadIdx.x == 0) base = atomicAdd(a.nrows, wsum[0] + wsum[1] + wsum[2] + wsum[3]);
+    __syncthreads();
+    if (k >= a.l) return;
+    int row = base + __popcll(b & ((1ull << lane) - 1));
+    for (int v = 0; v < wv; ++v) row += wsum[v];
+    gptr(a.pos)[k] = any ? row : -1;
+    if (any) gptr(a.perm)[row] = (int32_t)k;
+}
+
+hipError_t launch_row_perm(const LaunchCtx &lc, const RowPermArgs &a) {
+    return plain_launch<RowPermArgs, row_perm_body>(lc, KF_PARITY, a, blocks_of(a));
 }
 
 hipError_t launch_support(const LaunchCtx &lc, const SupportArgs &a) {
@@ -782,6 +808,15 @@ __device__ __forceinline__ void fwd_region(const FwdOps<FM, FN, NL> &cur, FwdOps
     interleave_half<0, FM * FN, 16 * FM + 4 + (F8 ? 4 * FM : 0)>();
 }
 
+// Observable blocks of the forward: those with a row (RowPerm).
+template <int FM>
+__device__ __forceinline__ int64_t fwd_blocks(const FwdArgs &a) {
+    const int64_t all = a.l_pad / (32 * FM);
+    if (!a.nrows) return all;
+    const int n = __builtin_amdgcn_readfirstlane(gptr(a.nrows)[0]);
+    return (n + 32 * FM - 1) / (32 * FM);
+}
+
 // Decomposition shared by both forward kernels.
 struct FwdUnit {
     int64_t sb, ob, split, w0, w1;
@@ -835,7 +870,7 @@ __device__ __forceinline__ void fwd_bf16_body(const FwdArgs &a, int64_t gu, int 
     const u32x4 IQP_GLOBAL *th8 = reinterpret_cast<const u32x4 IQP_GLOBAL *>(gptr(a.thl));
     float IQP_GLOBAL *__restrict__ E = gptr(a.E);
     const int64_t l_pad = a.l_pad, s_pad = a.s_pad, mw = a.m_pad / 64;
-    const int64_t n_ob = l_pad / (32 * FM), n_sb = s_pad / (32 * FN);
+    const int64_t n_ob = fwd_blocks<FM>(a), n_sb = s_pad / (32 * FN);
     const int64_t wps = ceil_div(mw, a.splits);
     FwdUnit U;
     fwd_unit(U, gu, n_ob, n_sb, mw, wps);
@@ -1056,8 +1091,11 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs &a, int64_t gu, int t
 // hi, mid and the FP8 third limb).
 template <int FM, int FN, int NL>
 __global__ __launch_bounds__(256, 1) void phase_fwd_bf16_kernel(FwdArgs a, int64_t units) {
-    const int64_t gu = xcd_remap(blockIdx.x, gridDim.x);
-    if (gu >= units) return;  // uniform over the workgroup
+    // fewer where observables are left out: the rest, spread over the XCDs
+    if (a.nrows)
+        units = fwd_blocks<FM>(a) * ceil_div(a.s_pad / (32 * FN), 4) * a.splits;
+    if ((int64_t)blockIdx.x >= units) return;  // uniform over the workgroup
+    const int64_t gu = xcd_remap(blockIdx.x, units);
     fwd_bf16_body<FM, FN, 2, NL == 3>(a, gu, (int)threadIdx.x);
 }
 
@@ -1166,11 +1204,13 @@ __device__ __forceinline__ void epilogue_unit(const EpiArgs &a, uint32_t unit, i
     const int64_t k = unit / nchunk, ch = unit - (uint32_t)k * nchunk;
     constexpr int kQ = (int)(kEpiChunk / kLanes);
     const int left = (int)(s - ch * kEpiChunk < kEpiChunk ? s - ch * kEpiChunk : kEpiChunk);
-    const float IQP_GLOBAL *row = E + k * s_pad + ch * kEpiChunk;
+    // an observable of weight 0 has no row: its phases are 0
+    const int64_t er = a.pos ? __builtin_amdgcn_readfirstlane(gptr(a.pos)[k]) : k;
+    const float IQP_GLOBAL *row = E + er * s_pad + ch * kEpiChunk;
     double e[kQ];
 #pragma unroll
     for (int q = 0; q < kQ; ++q) e[q] = 0.0;
-    for (int64_t sp = 0; sp < splits; ++sp) {
+    for (int64_t sp = 0; sp < (er < 0 ? 0 : splits); ++sp) {
         float v[kQ];
 #pragma unroll
         for (int q = 0; q < kQ; ++q) v[q] = lane + q * kLanes < left ? row[lane + q * kLanes] : 0.0f;

@@ -184,11 +184,20 @@ __device__ __forceinline__ void lut_row<true>(const SparseBwdArgs &a, int64_t k,
     }
 }
 
+// An observable of weight 0 commutes with every generator (most operators of a
+// wide kernel bandwidth): its blocks need no row of C. (Uniform over the block.)
+__device__ __forceinline__ bool weight_zero(const SampleParity &b, int64_t k) {
+    uint64_t any = 0ull;
+    for (int w = 0; w < b.W; ++w) any |= gptr(b.ops)[k * b.W + w];
+    return any == 0ull;
+}
+
 template <bool kIndep>
 __device__ __forceinline__ void sparse_bwd_lut_body(const SparseBwdArgs &a, int64_t blk) {
     // chunk-major: the blocks that run together read one 128-byte column
     // of the parity rows (fewer HBM fetches than observable-major order)
     const int64_t ch = blk / a.l, k = blk - ch * a.l;
+    if (weight_zero(a.bsrc, k)) return;
     const int tid = threadIdx.x, lane = tid & 63;
     __shared__ __attribute__((aligned(16))) float tab[kLutTables * 16];
     __shared__ int32_t lst[kLutList];
@@ -392,7 +401,7 @@ __device__ __forceinline__ void sparse_fwd_lut_body(const SparseFwdArgs &a, int6
             }
         }
     };
-    compact_row(gptr(a.crm) + k * a.Gw, a.Gw, lst, wsum, fill);
+    if (!weight_zero(a.bsrc, k)) compact_row(gptr(a.crm) + k * a.Gw, a.Gw, lst, wsum, fill);
 
     // T_k = the sum of the threads' shares (waves, then the 4 wave sums in order)
 #pragma unroll
