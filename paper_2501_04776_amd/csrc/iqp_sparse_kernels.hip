@@ -278,16 +278,16 @@ __device__ __forceinline__ void sparse_bwd_lut_body(const SparseBwdArgs &a, int6
 
 // Forward by table lookup. A block takes observable k and one chunk of
 // kEpiChunk samples; its waves take 4 of the chunk's 16 sample words each,
-// lane L sample 64 r + L of word r. The generators J_k are compacted into
+// 4 samples a lane (lut_sample). The generators J_k are compacted into
 // the LDS list as in the backward, and every 4 consecutive entries get a
 // 16-entry table of their angle sums,
 //   G_e[v] = sum_{b < 4, v_b = 1} t_{lst[4e + b]},  t_j = 2 theta'_j (FP32),
 // so that a sample's sum over the 64 entries 64g .. 64g + 63 is the sum of
 // 16 table reads indexed by its parity bits for those generators, 4 at a
-// time. Those bits come from a 64 x 64 bit transpose: lane L loads the
-// parity word of entry 64g + L for the wave's sample word, and after the
-// transpose lane L holds, for its sample, bit c = the parity of entry
-// 64g + c. The nibble offsets are formed as in the backward ((x << 2) and
+// time. Those bits come from an exchange over the wave: lane L loads the
+// parity words of entry 64g + L for the wave's samples, and lut_transpose
+// gives each lane all 64 entries' bits of its own 4. The nibble offsets are
+// formed as in the backward ((x << 2) and
 // (x >> 2) masked to 0x3C per byte) and a byte permute places each one
 // under the group's table base (g * 1024 bytes; the table within the group
 // is the LDS instruction's immediate offset). All lanes read one 16-entry
@@ -295,7 +295,11 @@ __device__ __forceinline__ void sparse_bwd_lut_body(const SparseBwdArgs &a, int6
 //   E_ki = T_k - 2 sum_{j in J_k, b_ij = 1} t_j,  T_k = sum_{j in J_k} t_j (FP64),
 // with the FP32 sum folded modulo the float nearest pi every 32 generators
 // (the whole multiples kept in an exact count), then reduced modulo 2 pi in
-// FP64 as the dense epilogue does.
+// FP64 as the dense epilogue does. Bound by the vector units: per sample and
+// 64 entries 20 instructions for the exchange, 24 for the offsets, 24 for the
+// sums and the fold (85 with a full 64x64 transpose per word, when n = 300,
+// 1000 observables, 10^4 samples took 0.309 ms and now 0.294; n = 1000, 10^5
+// gates, 2000 observables 1.02 and 0.92 ms).
 template <bool kIndep>
 __device__ __forceinline__ void lut_fwd_words(const SparseFwdArgs &a, int64_t k, int64_t sw,
                                               int64_t j, u32x4 (&wv)[2]);
@@ -333,6 +337,54 @@ __device__ __forceinline__ void lut_fwd_words<true>(const SparseFwdArgs &a, int6
     }
 }
 
+// The exchange before the forward's lookups. On entry lane e holds the parity
+// words of generator e (of 64) for 256 samples, dword q the samples 32 q ..
+// 32 q + 31; on return each lane holds all 64 generators' bits of 4 samples,
+// as nibbles of 4 generators, one table each. A lane's index bit is swapped
+// with a dword's (lane bits 5 and 4 by gfx950's register swaps, bit 2 by masked
+// DPP moves: no bit work) or with a bit's place inside the dword (lane bit 3
+// with bit 4, a DPP move and a byte select; lane bits 1 and 0 with bits 1 and
+// 0, so that the 4 generators of a table sit side by side). The samples' bits 2
+// and 3 stay inside the dword: which sample comes to which lane does not
+// matter, and 4 full 64x64 transposes would take 35 vector instructions and 2
+// swizzles a word where this takes 20. Table t (bits t3 t2 t1 t0) of sample r
+// (bits r1 r0) is the nibble r0 of byte 2 t1 + r1 of dword t3 t2 t0.
+__device__ __forceinline__ void lut_transpose(uint32_t (&d)[8], int lane) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {  // lane bit 5 with dword bit 2
+        const auto r = __builtin_amdgcn_permlane32_swap(d[q], d[q + 4], false, false);
+        d[q] = r[0];
+        d[q + 4] = r[1];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; q += (q & 1) ? 3 : 1) {  // lane bit 4 with dword bit 1
+        const auto r = __builtin_amdgcn_permlane16_swap(d[q], d[q + 2], false, false);
+        d[q] = r[0];
+        d[q + 2] = r[1];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; q += 2) {  // lane bit 2 with dword bit 0
+        const uint32_t x = d[q], y = d[q + 1];
+        d[q] = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)y, 0x114, 0xF, 0xA, false);
+        d[q + 1] = (uint32_t)__builtin_amdgcn_update_dpp((int)y, (int)x, 0x104, 0xF, 0x5, false);
+    }
+    const uint32_t sel = (lane & 8) ? 0x03020706u : 0x05040100u;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)  // lane bit 3 with bit 4
+        d[q] = __builtin_amdgcn_perm(lane_xor<8>(d[q]), d[q], sel);
+#pragma unroll
+    for (int q = 0; q < 8; q += 2) {
+        small_stage<2, 1, 0x33333333u>(d[q], d[q + 1], lane);
+        small_stage<1, 0, 0x55555555u>(d[q], d[q + 1], lane);
+    }
+}
+
+// The sample (of the wave's 256) that lane holds as its r-th after
+// lut_transpose.
+__device__ __forceinline__ int lut_sample(int lane, int r) {
+    return (lane & 3) | (r << 2) | ((lane & 8) << 1) | ((lane & 4) << 3) | ((lane & 48) << 2);
+}
+
 template <bool kIndep>
 __device__ __forceinline__ void sparse_fwd_lut_body(const SparseFwdArgs &a, int64_t blk) {
     const int64_t nchunk = ceil_div(a.s, kEpiChunk);
@@ -368,35 +420,38 @@ __device__ __forceinline__ void sparse_fwd_lut_body(const SparseFwdArgs &a, int6
             const int e = 64 * g + lane;
             u32x4 wv[2] = {u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}};
             if (e < n) lut_fwd_words<kIndep>(a, k, sw, lst[e], wv);
+            uint32_t d[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) d[q] = wv[q / 4][q % 4];
+            lut_transpose(d, lane);
             const uint32_t gb = (uint32_t)g * 1024u;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint64_t xw = ((uint64_t)wv[r / 2][2 * (r % 2) + 1] << 32) |
-                                    wv[r / 2][2 * (r % 2)];
-                const uint64_t yb = transpose64(xw, lane);
-                // m[2h] byte e': 4 * nibble 2e' of dword h, m[2h + 1]: nibble 2e' + 1
-                uint32_t m[4];
+            for (int c = 0; c < 2; ++c) {
+                uint32_t m[8];  // byte i: 4 * its low (c = 0) or high nibble
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t d = (uint32_t)(yb >> (32 * h));
-                    m[2 * h] = (d << 2) & 0x3C3C3C3Cu;
-                    m[2 * h + 1] = (d >> 2) & 0x3C3C3C3Cu;
-                }
-                float v[16];
+                for (int q = 0; q < 8; ++q)
+                    m[q] = (c == 0 ? d[q] << 2 : d[q] >> 2) & 0x3C3C3C3Cu;
 #pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const uint32_t o = __builtin_amdgcn_perm(
-                        gb, m[2 * (q / 8) + q % 2], 0x07060500u | (uint32_t)((q % 8) / 2));
-                    v[q] = *reinterpret_cast<const float *>(tb + q * 64 + o);
-                }
+                for (int o = 0; o < 2; ++o) {
+                    const int r = 2 * o + c;
+                    float v[16];
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const float p = ((v[8 * h] + v[8 * h + 1]) + (v[8 * h + 2] + v[8 * h + 3])) +
-                                    ((v[8 * h + 4] + v[8 * h + 5]) + (v[8 * h + 6] + v[8 * h + 7]));
-                    acc[r] += p;
-                    const float qq = rintf(acc[r] * kInvPiF);
-                    acc[r] = fmaf(-qq, kPiF, acc[r]);
-                    kpi[r] += qq;
+                    for (int t = 0; t < 16; ++t) {
+                        const uint32_t at = __builtin_amdgcn_perm(
+                            gb, m[(t & 1) | ((t >> 1) & 6)],
+                            0x07060500u | (uint32_t)(2 * ((t >> 1) & 1) + o));
+                        v[t] = *reinterpret_cast<const float *>(tb + t * 64 + at);
+                    }
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const float p =
+                            ((v[8 * h] + v[8 * h + 1]) + (v[8 * h + 2] + v[8 * h + 3])) +
+                            ((v[8 * h + 4] + v[8 * h + 5]) + (v[8 * h + 6] + v[8 * h + 7]));
+                        acc[r] += p;
+                        const float qq = rintf(acc[r] * kInvPiF);
+                        acc[r] = fmaf(-qq, kPiF, acc[r]);
+                        kpi[r] += qq;
+                    }
                 }
             }
         }
@@ -413,7 +468,7 @@ __device__ __forceinline__ void sparse_fwd_lut_body(const SparseFwdArgs &a, int6
     float IQP_GLOBAL *ph = a.phase_out ? gptr(a.phase_out) + k * a.s : nullptr;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int64_t i = (sw + r) * 64 + lane;
+        const int64_t i = sw * 64 + lut_sample(lane, r);
         if (i < a.s) {
             const double e = T - 2.0 * ((double)acc[r] + (double)kpi[r] * (double)kPiF);
             const double kk = rint(e * IQP_INV_TWO_PI);
@@ -453,7 +508,7 @@ __device__ __forceinline__ void sparse_fwd_lut_body(const SparseFwdArgs &a, int6
 // (at most kMaxBlocks blocks), the strided form takes them in steps of the
 // grid's size, with a barrier before a block's next unit rewrites its LDS;
 // it is a separate instantiation because the loop costs the body registers
-// (85 and 93 instead of 77 and 76 VGPRs: a wave per SIMD).
+// (98 and 99 instead of 77 and 80 VGPRs: two waves per SIMD).
 template <bool kIndep, bool kStrided>
 __global__ __launch_bounds__(256) void sparse_fwd_lut_kernel(SparseFwdArgs a, int64_t units) {
     if (!kStrided) {
