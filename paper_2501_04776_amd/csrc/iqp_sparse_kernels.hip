@@ -55,8 +55,8 @@ hipError_t launch_sparse_bound(const LaunchCtx &lc, const SparseBoundArgs &a) {
     return plain_launch<SparseBoundArgs, sparse_bound_body>(lc, KF_WEIGHTS, a, blocks_of(a));
 }
 
-// Gradient by table lookup. A block takes observable k and one chunk of
-// kEpiChunk samples. Thread t computes S_ki for the four samples 4t .. 4t + 3
+// Gradient by table lookup. A block takes observable k and kC (1 or 2) chunks
+// of kEpiChunk samples, each with tables of its own. Thread t computes S_ki for the four samples 4t .. 4t + 3
 // of the chunk and writes their 16 signed sums
 //   L_t[v] = sum_{b < 4} (-1)^{v_b} S_{k, c + 4t + b},  v = 0 .. 15,
 // so that, with v_t(j) the nibble of generator j's parity bits over those
@@ -73,6 +73,16 @@ hipError_t launch_sparse_bound(const LaunchCtx &lc, const SparseBoundArgs &a) {
 // never conflict.
 constexpr int kLutTables = (int)(kEpiChunk / 4);  // one per thread of the block
 constexpr int kLutList = 1024;                    // generators per list fill
+// Gradient blocks take two chunks of samples once that leaves kPairBlocks of
+// them: half the atomics into the gates' sums, which bound the kernel once the
+// parity rows outgrow an L2, and half the compactions. Whole gradients with two
+// and with one chunk a block: n = 300, 40000 gates, 10^4 samples 0.114 and
+// 0.154 ms at 400 observables, 0.301 and 0.420 at 1600; n = 1000, 10^5 gates
+// 1.16 and 1.99 ms. With fewer blocks than the chip runs at once the longer
+// ones are the time: 1.03 to 1.3 times it at 200 blocks and under, 0.81 to
+// 0.96 at 400. Three chunks a block (tables of 48 KB) took 0.90 to 1.06 of the
+// time of two, four 1.00 to 1.27.
+constexpr int64_t kPairBlocks = 320;
 
 static_assert(kLutTables == 256, "one table per thread of a 256-thread block");
 
@@ -192,24 +202,27 @@ __device__ __forceinline__ bool weight_zero(const SampleParity &b, int64_t k) {
     return any == 0ull;
 }
 
-template <bool kIndep>
+template <bool kIndep, int kC>
 __device__ __forceinline__ void sparse_bwd_lut_body(const SparseBwdArgs &a, int64_t blk) {
-    // chunk-major: the blocks that run together read one 128-byte column
+    // chunk-major: the blocks that run together read the same 128-byte columns
     // of the parity rows (fewer HBM fetches than observable-major order)
-    const int64_t ch = blk / a.l, k = blk - ch * a.l;
+    const int64_t cg = blk / a.l, k = blk - cg * a.l, ch0 = cg * kC;
+    const int64_t left = ceil_div(a.s, kEpiChunk) - ch0;
+    const int nc = left < kC ? (int)left : kC;
     if (weight_zero(a.bsrc, k)) return;
     const int tid = threadIdx.x, lane = tid & 63;
-    __shared__ __attribute__((aligned(16))) float tab[kLutTables * 16];
+    __shared__ __attribute__((aligned(16))) float tab[kC * kLutTables * 16];
     __shared__ int32_t lst[kLutList];
     __shared__ int wsum[2][4];
 
-    // the tables of this chunk
-    {
-        const double al = gptr(a.coef)[2 * k], be = gptr(a.coef)[2 * k + 1];
+    // the tables of these chunks
+    const double al = gptr(a.coef)[2 * k], be = gptr(a.coef)[2 * k + 1];
+#pragma unroll 1
+    for (int c = 0; c < nc; ++c) {
         float S[4];
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-            const int64_t i = ch * kEpiChunk + 4 * tid + b;
+            const int64_t i = (ch0 + c) * kEpiChunk + 4 * tid + b;
             float v = 0.0f;
             if (i < a.s) {
                 float sn, cs;
@@ -221,7 +234,7 @@ __device__ __forceinline__ void sparse_bwd_lut_body(const SparseBwdArgs &a, int6
         // x[u] over samples 0, 1 and y[u] over samples 2, 3, bit set = minus
         const float x[4] = {S[0] + S[1], S[1] - S[0], S[0] - S[1], -S[0] - S[1]};
         const float y[4] = {S[2] + S[3], S[3] - S[2], S[2] - S[3], -S[2] - S[3]};
-        float4 *row = reinterpret_cast<float4 *>(tab + tid * 16);
+        float4 *row = reinterpret_cast<float4 *>(tab + (c * kLutTables + tid) * 16);
 #pragma unroll
         for (int h = 0; h < 4; ++h)
             row[h] = make_float4(x[0] + y[h], x[1] + y[h], x[2] + y[h], x[3] + y[h]);
@@ -234,41 +247,45 @@ __device__ __forceinline__ void sparse_bwd_lut_body(const SparseBwdArgs &a, int6
         for (int g = wave_id() * 64 + lane; g - lane < n; g += 256) {
             if (g >= n) continue;
             const int64_t j = lst[g];
-            u32x4 wv[8];
-            lut_row<kIndep>(a, k, ch, j, wv);
-            float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            const char *tb = reinterpret_cast<const char *>(tab);
+            long long add = 0;
+#pragma unroll 1
+            for (int c = 0; c < nc; ++c) {
+                u32x4 wv[8];
+                lut_row<kIndep>(a, k, ch0 + c, j, wv);
+                float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+                const char *tb = reinterpret_cast<const char *>(tab + c * kLutTables * 16);
 #pragma unroll
-            for (int r = 0; r < kSpWords; ++r) {
-                // word r holds nibbles t = 16 r + e (bits 4e .. 4e + 3): byte
-                // e' of x[2h] is 4 times nibble 8h + 2e', of x[2h + 1] 4 times
-                // nibble 8h + 2e' + 1 (kept opaque so that each byte costs one
-                // extract instead of a shift and a mask)
-                uint32_t x[4];
+                for (int r = 0; r < kSpWords; ++r) {
+                    // word r holds nibbles t = 16 r + e (bits 4e .. 4e + 3): byte
+                    // e' of x[2h] is 4 times nibble 8h + 2e', of x[2h + 1] 4 times
+                    // nibble 8h + 2e' + 1 (kept opaque so that each byte costs one
+                    // extract instead of a shift and a mask)
+                    uint32_t x[4];
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t d = wv[r / 2][2 * (r % 2) + h];
-                    x[2 * h] = (d << 2) & 0x3C3C3C3Cu;
-                    x[2 * h + 1] = (d >> 2) & 0x3C3C3C3Cu;
-                    asm volatile("" : "+v"(x[2 * h]), "+v"(x[2 * h + 1]));
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t d = wv[r / 2][2 * (r % 2) + h];
+                        x[2 * h] = (d << 2) & 0x3C3C3C3Cu;
+                        x[2 * h + 1] = (d >> 2) & 0x3C3C3C3Cu;
+                        asm volatile("" : "+v"(x[2 * h]), "+v"(x[2 * h + 1]));
+                    }
+                    float v[16];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const uint32_t o = (x[e / 4 % 2 + 2 * (e / 8)] >> (8 * (e % 4))) & 0xFFu;
+                        const int t = 16 * r + 8 * (e / 8) + 2 * (e % 4) + e / 4 % 2;
+                        v[e] = *reinterpret_cast<const float *>(tb + t * 64 + o);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[e] += v[e] + v[e + 8];
                 }
-                float v[16];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const uint32_t o = (x[e / 4 % 2 + 2 * (e / 8)] >> (8 * (e % 4))) & 0xFFu;
-                    const int t = 16 * r + 8 * (e / 8) + 2 * (e % 4) + e / 4 % 2;
-                    v[e] = *reinterpret_cast<const float *>(tb + t * 64 + o);
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[e] += v[e] + v[e + 8];
+                const float tot = ((acc[0] + acc[1]) + (acc[2] + acc[3])) +
+                                  ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+                if (isfinite(tot))
+                    add += llrint((double)tot * scale);
+                else
+                    atomicOr((unsigned long long *)&gptr(a.acc)[a.m_pad], 1ull);
             }
-            const float tot = ((acc[0] + acc[1]) + (acc[2] + acc[3])) +
-                              ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-            if (isfinite(tot))
-                atomicAdd((unsigned long long *)&gptr(a.acc)[j],
-                          (unsigned long long)llrint((double)tot * scale));
-            else
-                atomicOr((unsigned long long *)&gptr(a.acc)[a.m_pad], 1ull);
+            atomicAdd((unsigned long long *)&gptr(a.acc)[j], (unsigned long long)add);
         }
     };
 
@@ -521,14 +538,14 @@ __global__ __launch_bounds__(256) void sparse_fwd_lut_kernel(SparseFwdArgs a, in
     }
 }
 
-template <bool kIndep, bool kStrided>
+template <bool kIndep, bool kStrided, int kC>
 __global__ __launch_bounds__(256) void sparse_bwd_lut_kernel(SparseBwdArgs a, int64_t units) {
     if (!kStrided) {
-        sparse_bwd_lut_body<kIndep>(a, (int64_t)blockIdx.x);
+        sparse_bwd_lut_body<kIndep, kC>(a, (int64_t)blockIdx.x);
         return;
     }
     for (int64_t b = blockIdx.x; b < units; b += gridDim.x) {
-        sparse_bwd_lut_body<kIndep>(a, b);
+        sparse_bwd_lut_body<kIndep, kC>(a, b);
         __syncthreads();
     }
 }
@@ -568,25 +585,33 @@ hipError_t launch_sparse_fwd(const LaunchCtx &lc, const SparseFwdArgs &a) {
     return e;
 }
 
-hipError_t launch_sparse_bwd(const LaunchCtx &lc, const SparseBwdArgs &a) {
-    const int64_t units = a.l * ceil_div(a.s, kEpiChunk);
-    if (units <= 0) return hipSuccess;
+template <int kC>
+static void launch_bwd_lut(const LaunchCtx &lc, const SparseBwdArgs &a) {
+    const int64_t units = a.l * ceil_div(a.s, kC * kEpiChunk);
     const unsigned blocks = (unsigned)lut_grid(units);
-    hipEvent_t ev;
-    timed_begin(lc, KF_BWD, &ev);
     const bool strided = (int64_t)blocks < units;
     if (a.bsrc.xt && strided)
-        hipLaunchKernelGGL((sparse_bwd_lut_kernel<true, true>), dim3(blocks), dim3(256), 0,
+        hipLaunchKernelGGL((sparse_bwd_lut_kernel<true, true, kC>), dim3(blocks), dim3(256), 0,
                            lc.stream, a, units);
     else if (a.bsrc.xt)
-        hipLaunchKernelGGL((sparse_bwd_lut_kernel<true, false>), dim3(blocks), dim3(256), 0,
+        hipLaunchKernelGGL((sparse_bwd_lut_kernel<true, false, kC>), dim3(blocks), dim3(256), 0,
                            lc.stream, a, units);
     else if (strided)
-        hipLaunchKernelGGL((sparse_bwd_lut_kernel<false, true>), dim3(blocks), dim3(256), 0,
+        hipLaunchKernelGGL((sparse_bwd_lut_kernel<false, true, kC>), dim3(blocks), dim3(256), 0,
                            lc.stream, a, units);
     else
-        hipLaunchKernelGGL((sparse_bwd_lut_kernel<false, false>), dim3(blocks), dim3(256), 0,
+        hipLaunchKernelGGL((sparse_bwd_lut_kernel<false, false, kC>), dim3(blocks), dim3(256), 0,
                            lc.stream, a, units);
+}
+
+hipError_t launch_sparse_bwd(const LaunchCtx &lc, const SparseBwdArgs &a) {
+    if (a.l <= 0 || a.s <= 0) return hipSuccess;
+    hipEvent_t ev;
+    timed_begin(lc, KF_BWD, &ev);
+    if (a.l * ceil_div(a.s, 2 * kEpiChunk) >= kPairBlocks)
+        launch_bwd_lut<2>(lc, a);
+    else
+        launch_bwd_lut<1>(lc, a);
     hipError_t e = hipGetLastError();
     timed_end(lc, KF_BWD, ev);
     return e;
