@@ -50,7 +50,10 @@ typedef enum {
 } iqp_status;
 
 /* Arithmetic of the phase contraction E = C Theta B^T.
- *   IQP_FP32:        2 theta_j in FP32, one FP32 matrix-core product per term.
+ *   IQP_FP32:        2 theta_j in FP32, one FP32 matrix-core product per term;
+ *                    single-problem calls of 2^31 terms and more whose C is
+ *                    sparse add the non-zero entries alone, in the same order
+ *                    and with the same result.
  *   IQP_SPLIT_BF16:  2 theta_j = hi + lo with hi, lo BF16 (round to nearest
  *                    even), two BF16 matrix-core products per term (the +-1
  *                    and 0/1 parity operands are exact in BF16), FP32
@@ -139,8 +142,8 @@ size_t iqp_workspace_bytes(int call, const iqp_circuit *c, int64_t l, int64_t s,
 
 /* Parity bit matrix (the exponents of B = (-1)^{Z G^T} and of
  * C = 1 - (-1)^{A G^T}, Sec. 2.2): bit (r, c) = popcount(row_r AND col_c) mod 2.
- * Computed bit-sliced: the rows are transposed into per-qubit bit columns and
- * the parity against col_c is the XOR of the columns in col_c's support, so
+ * Computed from bit columns: the rows are transposed into per-qubit columns
+ * and the parity against col_c is the XOR of the columns in col_c's support, so
  * the cost grows with the weight of the col rows (pass the sparse operand,
  * e.g. the generators, as cols).
  *   rows      device [n_rows][W], cols device [n_cols][W]
@@ -247,7 +250,7 @@ int iqp_expval_indep_grad(const iqp_circuit *c, int64_t l, const uint64_t *ops, 
  * the circuit, where gate j flips the bits of g_j with probability
  * sin^2(theta_j). Its expectation values are exact and classical:
  *     <Z_{a_k}> = prod_{j : a_k . g_j odd} cos(2 theta_j)   (eq. expval_bitflip)
- * computed in FP64 from the C parity bits (a sum of log|cos| with a sign
+ * computed in FP64 from C's parities (a sum of log|cos| with a sign
  * parity and a count of zero factors per observable).
  *   ops        device [l][W], l >= 1
  *   mean       device [l] the exact expectation values
