@@ -306,6 +306,12 @@ void make_plan(Plan &P, const PlanParts &parts, int64_t n, int64_t m, int64_t l,
         P.o_E = carve(cur, (size_t)P.tc.splits * P.l_pad * P.s_pad * 4);
         P.o_part = carve(cur, (size_t)l * P.nchunk * 2 * 8);
         P.o_rowsum = carve(cur, (size_t)l * 2 * 8);
+        // Every gated kernel of an FP32 forward reads the counter of C's entries,
+        // so it lives in the one of the two sums that none of them writes: with
+        // several chunks per observable they write the chunks' sums and finalize
+        // the row sums; with one chunk they write the row sums themselves and the
+        // chunks' sums stay unused.
+        P.o_nnz = P.nchunk > 1 ? P.o_rowsum : P.o_part;
     }
     if (P.phi) P.o_phi = carve(cur, (size_t)l * s * 4);
     if (P.bwd) {
@@ -539,13 +545,13 @@ static hipError_t launch_fwd(const LaunchCtx &lc, const Plan &P, const FwdArgs &
 static int run_forward_fp32(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
                             const uint64_t *samples, void *ws, const LaunchCtx &lc,
                             float *phase_out, double *mean, double *se, double *rowsum) {
-    // the counter lives in the row sums, which the last step writes, and B^T
-    // (row-major) where the matrix cores' B would be: one of the two is used
+    // B^T (row-major) takes the place of the matrix cores' B: one of the two is
+    // used
     ChainGate gate;
-    gate.nnz = at<unsigned long long>(ws, P.o_rowsum);
+    gate.nnz = at<unsigned long long>(ws, P.o_nnz);
     gate.limit = (unsigned long long)(chain_density(P) * (double)P.l * (double)P.m);
     ThetaArgs th = theta_args(P, c->theta, ws);
-    th.nnz = at<unsigned long long>(ws, P.o_rowsum);
+    th.nnz = at<unsigned long long>(ws, P.o_nnz);
     IQP_TRY(launch_prep(lc, th, support_args(P, c->gens, ws)), "theta_prep, support");
     IQP_TRY(launch_parity(lc, IQP_BITS_TILED32, parity_c_args(P, c->gens, ops, ws)), "parity(C)");
     IQP_TRY(launch_count(lc, CountArgs{at<uint64_t>(ws, P.o_cbits), P.l_pad, P.mw, th.nnz}),
@@ -600,8 +606,8 @@ static int run_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
     // Operators drawn for a wide kernel bandwidth are mostly of weight 0, and
     // their rows of the product are all zero: the MMD forward leaves them out
     // from the size on where the product takes well over the extra launch
-    // (2^34 terms, 40 us). The row table lives in the row sums, which the last
-    // step writes.
+    // (2^34 terms, 40 us). The row table lives in the row sums, which finalize
+    // writes when there is more than one chunk.
     const bool drop = P.mmd && P.prec != IQP_FP32 && pc.rw && P.nchunk > 1 &&
                       (double)P.l * (double)P.s * (double)P.m >= 17179869184.0;
     if (drop) {

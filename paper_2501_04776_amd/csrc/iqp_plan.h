@@ -74,6 +74,7 @@ struct Plan {
     size_t o_btbits = 0;                  // B^T: samples against generators, transposed
     size_t o_sup = 0;                     // support lists of the generators
     size_t o_enc = 0, o_stat = 0;         // bitflip circuits: factors, per-observable sums
+    size_t o_nnz = 0;                     // FP32 forward: counter of C's entries (ChainGate)
     size_t o_gcnt = 0, o_glist = 0;       // gate lists of the backward
     size_t o_acc = 0, o_scale = 0;        // sparse gradient: int64 sums (+ flag), scale
     int64_t ldz = 0, lda = 0;
