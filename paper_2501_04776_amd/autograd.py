@@ -31,10 +31,10 @@ class IQPExpval(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_mean, grad_se):
         theta, gens, ops, samples, ph = ctx.saved_tensors
-        if grad_mean is None:
-            return (None,) * 6
         if grad_se is not None and bool((grad_se != 0).any()):
             raise RuntimeError("the standard error is not differentiable")
+        if grad_mean is None:  # the consumer of the mean has no gradient
+            grad_mean = torch.zeros(ops.shape[0], dtype=torch.float64, device=theta.device)
         circ = api.Circuit(ctx.n_qubits, gens, theta.detach())
         g = api.iqp_expval_grad(circ, ops, samples, grad_mean.to(torch.float64).contiguous(),
                                 phase_save=ph if ph.numel() else None, precision=ctx.precision)
