@@ -440,7 +440,7 @@ struct BitflipSumArgs {
     int32_t *pcode;
 };
 inline size_t lds_of(const BitflipSumArgs &a) {
-    const size_t sums = (size_t)64 * a.par.rw * 12, bits = lds_of(a.par);
+    const size_t sums = (size_t)64 * a.par.rw * 20, bits = lds_of(a.par);
     return sums > bits ? sums : bits;
 }
 struct BitflipFinishArgs {

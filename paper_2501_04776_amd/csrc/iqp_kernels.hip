@@ -2976,11 +2976,21 @@ hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a) {
 //             S_k < kDeep, whose e^{S_k} would lose bits near the smallest
 //             doubles, keep e^{S_k - log|c_j|} per entry.
 // Partials per gate chunk and per observable chunk are added in order by the
-// finishing kernels. Bound by the vector instructions of the transposes and of
-// the walks over set bits, two blocks of LDS per CU. 1000 qubits, 10^5 gates,
-// 10^4 observables (1.1 % of C non-zero): C's parities and the forward 81 + 210
-// -> 109 us, the gradient's and the gradient 83 + 383 -> 99 us.
+// finishing kernels. An absolute error of S_k is a relative one of e^{S_k}, and
+// S_k reaches the hundreds, so the partials of S_k are added with their rounding
+// carried along (add_exact) into the exponential. Bound by the vector
+// instructions of the transposes and of the walks over set bits, two blocks of
+// LDS per CU. 1000 qubits, 10^5 gates, 10^4 observables (1.1 % of C non-zero): C's
+// parities and the forward 81 + 210 -> 109 us, the gradient's and the gradient
+// 83 + 383 -> 99 us.
 constexpr double kDeep = -700.0;
+
+// sum + err += x, with the rounding of the sum kept in err (Knuth's two-sum).
+__device__ __forceinline__ void add_exact(double &sum, double &err, double x) {
+    const double s = sum + x, b = s - sum;
+    err += (sum - (s - b)) + (x - b);
+    sum = s;
+}
 
 template <int RW>
 __device__ __forceinline__ void bitflip_sum(const BitflipSumArgs &a, int64_t blk,
@@ -3014,21 +3024,26 @@ __device__ __forceinline__ void bitflip_sum(const BitflipSumArgs &a, int64_t blk
             if (rw0 + i >= p.Rw) break;  // uniform over the wave
             uint64_t y = transpose64(x[i], lane);
             code[i] = (code[i] ^ (__popcll(y & negm) & 1)) + 2 * __popcll(y & zerom);
+            double t = 0.0;  // a word's sum apart: shorter chains, less rounding
             while (y) {
-                S[i] += logs[wv][__builtin_ctzll(y)];
+                t += logs[wv][__builtin_ctzll(y)];
                 y &= y - 1;
             }
+            S[i] += t;
         }
     }
     __syncthreads();  // Xs is read no more: it holds the block's sums now
-    double *bs = reinterpret_cast<double *>(Xs);
-    int *bc = reinterpret_cast<int *>(bs + 64 * RW);
+    double *bs = reinterpret_cast<double *>(Xs), *be = bs + 64 * RW;  // sums, their rounding
+    int *bc = reinterpret_cast<int *>(be + 64 * RW);
     for (int v = 0; v < 4; ++v) {
         if (wv == v) {
 #pragma unroll
             for (int i = 0; i < RW; ++i) {
                 const int o = i * 64 + lane;
-                bs[o] = v ? bs[o] + S[i] : S[i];
+                double sum = v ? bs[o] : 0.0, err = v ? be[o] : 0.0;
+                add_exact(sum, err, S[i]);
+                bs[o] = sum;
+                be[o] = err;
                 // parities XOR, counts add
                 bc[o] = v ? ((bc[o] ^ code[i]) & 1) + (bc[o] & ~1) + (code[i] & ~1) : code[i];
             }
@@ -3038,7 +3053,7 @@ __device__ __forceinline__ void bitflip_sum(const BitflipSumArgs &a, int64_t blk
     for (int o = threadIdx.x; o < 64 * RW; o += 256) {
         const int64_t k = rw0 * 64 + o;
         if (k < a.l_pad) {
-            gptr(a.psum)[gc * a.l_pad + k] = bs[o];
+            gptr(a.psum)[gc * a.l_pad + k] = bs[o] + be[o];
             gptr(a.pcode)[gc * a.l_pad + k] = bc[o];
         }
     }
@@ -3059,16 +3074,19 @@ __device__ __forceinline__ void bitflip_sum_body(const BitflipSumArgs &a, int64_
 __device__ __forceinline__ void bitflip_finish_body(const BitflipFinishArgs &a, int64_t blk) {
     const int64_t k = blk * 256 + threadIdx.x;
     if (k >= a.l) return;
-    double S = 0.0;
+    double S = 0.0, err = 0.0;
     int neg = 0, zeros = 0;
     for (int64_t gc = 0; gc < a.ngc; ++gc) {
-        S += gptr(a.psum)[gc * a.l_pad + k];
+        add_exact(S, err, gptr(a.psum)[gc * a.l_pad + k]);
         const int c = gptr(a.pcode)[gc * a.l_pad + k];
         neg ^= c & 1;
         zeros += c >> 1;
     }
-    const double sgn = neg ? -1.0 : 1.0;
-    const double prod = sgn * exp(S);
+    // S + err = hi + lo, and e^{hi + lo} = e^hi (1 + lo)
+    const double hi = S + err, lo = (S - hi) + err;
+    S = hi;
+    const double sgn = neg ? -1.0 : 1.0, ex = exp(S);
+    const double prod = sgn * fma(ex, lo, ex);
     if (a.mean) gptr(a.mean)[k] = zeros ? 0.0 : prod;
     if (!a.grad_mean) return;
     const double u = gptr(a.grad_mean)[k];
@@ -3115,10 +3133,12 @@ __device__ __forceinline__ void bitflip_dot(const BitflipDotArgs &a, int64_t blk
             uint64_t d = zero ? 0ull : y & deep[i];
             uint64_t z = zero ? y : 0ull;
             y = zero ? 0ull : y;
+            double t = 0.0;  // a word's sum apart, as in bitflip_sum
             while (y) {
-                acc += v[i * 64 + __builtin_ctzll(y)];
+                t += v[i * 64 + __builtin_ctzll(y)];
                 y &= y - 1;
             }
+            acc += t;
             while (z) {
                 acc += gptr(a.val)[2 * ((rw0 + i) * 64 + __builtin_ctzll(z)) + 1];
                 z &= z - 1;
