@@ -2973,8 +2973,8 @@ hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a) {
 //   gradient  sum over the lane's observables k of v_k = u_k sign_k e^{S_k},
 //             read from LDS; times 1 / c_j at the end. One exponential per
 //             observable instead of one per non-zero entry. Observables with
-//             S_k < kDeep, whose e^{S_k} would lose bits near the smallest
-//             doubles, keep e^{S_k - log|c_j|} per entry.
+//             S_k < kDeep or |v_k| < kTiny, which would lose bits near the
+//             smallest doubles, keep u_k e^{S_k - log|c_j|} per entry.
 // Partials per gate chunk and per observable chunk are added in order by the
 // finishing kernels. An absolute error of S_k is a relative one of e^{S_k}, and
 // S_k reaches the hundreds, so the partials of S_k are added with their rounding
@@ -2983,7 +2983,7 @@ hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a) {
 // LDS per CU. 1000 qubits, 10^5 gates, 10^4 observables (1.1 % of C non-zero): C's
 // parities and the forward 81 + 210 -> 109 us, the gradient's and the gradient
 // 83 + 383 -> 99 us.
-constexpr double kDeep = -700.0;
+constexpr double kDeep = -700.0, kTiny = 1e-300;
 
 // sum + err += x, with the rounding of the sum kept in err (Knuth's two-sum).
 __device__ __forceinline__ void add_exact(double &sum, double &err, double x) {
@@ -3069,8 +3069,9 @@ __device__ __forceinline__ void bitflip_sum_body(const BitflipSumArgs &a, int64_
     else bitflip_sum<1>(a, blk, parity_lds, logs);
 }
 
-// stat[k] as bitflip_fwd_body writes it; val[k] = u_k times the product over
-// the non-zero factors where none (val[2k]) or one (val[2k + 1]) is zero.
+// val[k] = u_k times the product over the non-zero factors where none (val[2k])
+// or one (val[2k + 1]) is zero; stat[k] = S_k and, where the entries keep their
+// own exponentials, sign_k u_k.
 __device__ __forceinline__ void bitflip_finish_body(const BitflipFinishArgs &a, int64_t blk) {
     const int64_t k = blk * 256 + threadIdx.x;
     if (k >= a.l) return;
@@ -3090,10 +3091,11 @@ __device__ __forceinline__ void bitflip_finish_body(const BitflipFinishArgs &a, 
     if (a.mean) gptr(a.mean)[k] = zeros ? 0.0 : prod;
     if (!a.grad_mean) return;
     const double u = gptr(a.grad_mean)[k];
-    const bool deep = zeros == 0 && S < kDeep;
+    const double v = u * (zeros == 0 ? prod : 0.0);
+    const bool deep = zeros == 0 && (S < kDeep || fabs(v) < kTiny);
     gptr(a.stat)[2 * k] = S;
     gptr(a.stat)[2 * k + 1] = deep ? sgn * u : 0.0;
-    gptr(a.val)[2 * k] = u * (zeros == 0 && !deep ? prod : 0.0);
+    gptr(a.val)[2 * k] = deep ? 0.0 : v;
     gptr(a.val)[2 * k + 1] = u * (zeros == 1 ? prod : 0.0);
 }
 

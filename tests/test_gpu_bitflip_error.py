@@ -56,3 +56,37 @@ def test_bitflip_error(shape):
         errs.append(np.abs((g[J] - ref) / ref).astype(np.float64).mean() / unit[k])
     errs = np.array(errs)
     assert np.sqrt((errs * errs).mean()) < 0.85
+
+
+def _deep(count):
+    """`count` gates of cos(1.5) and one of cos(2 theta) ~ 2e-8 on qubit 0."""
+    theta = np.full(count + 1, 0.75)
+    theta[count] = np.pi / 4 - 1e-8
+    return W.Workload("deep", 2, W.rows_from_lists([[0]] * (count + 1)), theta,
+                      W.rows_from_lists([[0], [1]]), np.zeros((1, 2), dtype=np.uint8))
+
+
+@pytest.mark.parametrize("count", [230, 250, 256, 260])
+@pytest.mark.parametrize("u0", [1.0, -1e-6, 1e-12, 1e-18, 1e-24])
+def test_bitflip_small_weight_times_small_product(count, u0):
+    # u e^S is among the subnormal doubles, or 0, where u e^{S - log|c|} is not
+    w = _deep(count)
+    dw = DevWorkload(w)
+    th = 2.0 * w.theta.astype(np.longdouble)
+    c = np.cos(th)
+    ref = -2.0 * np.sin(th) * u0 * np.prod(c) / c
+    circ = api.Circuit(w.n, dw.gens, dw.theta)
+    u = torch.tensor([u0, 3.0], dtype=torch.float64, device="cuda")
+    g = api.iqp_bitflip_expval_grad(circ, dw.ops, u).cpu().numpy()
+    normal = np.abs(ref) > 1e-306
+    # S and log|c_j| are rounded at 700 and under, a few times
+    assert (np.abs((g - ref) / ref)[normal] < 1e-12).all()
+    assert np.abs(g - ref)[~normal].max(initial=0.0) < 1e-318
+
+
+def test_bitflip_infinite_weight_of_a_deep_product():
+    w = _deep(260)  # S = -706
+    dw = DevWorkload(w)
+    circ = api.Circuit(w.n, dw.gens, dw.theta)
+    u = torch.tensor([np.inf, 3.0], dtype=torch.float64, device="cuda")
+    assert torch.isinf(api.iqp_bitflip_expval_grad(circ, dw.ops, u)).all()
