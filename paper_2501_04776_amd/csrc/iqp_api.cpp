@@ -665,7 +665,10 @@ static int run_backward(const Plan &P, const iqp_circuit *c, const uint64_t *ops
     // at full wave slots), at most cap to a row. C row-major takes the space of
     // the gate lists, the ranks that of the gradient partials and T that of the
     // weights, each of which the other way writes after the count or not at all.
+    // Its kernels take a block per observable and split, which one grid holds up
+    // to 2^24 - 1 of.
     const bool chain = P.prec == IQP_FP32 && P.tc.bsplits <= kChainMaxSplits &&
+                       P.l * P.tc.bsplits < ((int64_t)1 << 24) &&
                        (double)P.l * (double)P.s * (double)P.m >= kChainTerms;
     const int64_t cap = P.s_pad * P.l_pad / (P.l * P.tc.bsplits);
     ChainGate gate;
