@@ -2682,10 +2682,11 @@ static void batched(const LaunchCtx &lc, const void *args, const int64_t *off, i
 hipError_t launch_batched(const LaunchCtx &lc, int kind, const void *args, const int64_t *off,
                           int np, int64_t total, size_t lds) {
     if (total <= 0) return hipSuccess;
-    // the gate lists and the gradient sums take more blocks per gate than the
-    // other steps, so they may take several launches
-    if (np < 1 || (total > kMaxBlocks && kind != SK_GRAD && kind != SK_GATELIST))
-        return hipErrorInvalidConfiguration;
+    // the parities from rows, the gate lists and the gradient sums take more
+    // blocks than the other steps, so they may take several launches
+    const bool many = kind == SK_PARITY1 || kind == SK_PARITY4 || kind == SK_GATELIST ||
+                      kind == SK_GRAD;
+    if (np < 1 || (total > kMaxBlocks && !many)) return hipErrorInvalidConfiguration;
     static const int family[SK_COUNT] = {KF_THETA, KF_PARITY,  KF_PARITY, KF_PARITY, KF_EPI, KF_FIN,
                                          KF_WEIGHTS, KF_WEIGHTS, KF_GRAD, KF_PARITY, KF_PARITY,
                                          KF_PARITY, KF_PARITY};
