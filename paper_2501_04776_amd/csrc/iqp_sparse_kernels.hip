@@ -834,6 +834,9 @@ __device__ __forceinline__ void chain_bwd_body(const ChainBwdArgs &a, int64_t bl
     const glb<const uint64_t> bt = gptr(a.btbits);
     float IQP_GLOBAL *T = gptr(a.T) + (ks * a.l + k) * a.cap;
     auto fill = [&](int n) {
+        // no entry (an observable of weight 0, or a row of whole lists): no pass
+        // over the samples (uniform over the block)
+        if (n == 0) return;
         // gates of this wave: entries q 256 + 64 wave + lane
         const int left = n - wave * 64;
         const int nq = __builtin_amdgcn_readfirstlane(left <= 0 ? 0 : (left + 255) / 256);
