@@ -998,12 +998,11 @@ static int run_bitflip(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
                 "bitflip_chain");
         return IQP_OK;
     }
+    IQP_TRY(launch_parity(lc, IQP_BITS_TILED32, pc), "parity(C)");
     if (grad_mean)
-        IQP_TRY(launch_parity2(lc, IQP_BITS_TILED32, pc, IQP_BITS_TILED32_T,
-                               parity_ops_args(P, c->gens, ops, ws, 0, P.o_ctbits)),
-                "parity(C, C^T)");
-    else
-        IQP_TRY(launch_parity(lc, IQP_BITS_TILED32, pc), "parity(C)");
+        IQP_TRY(launch_parity(lc, IQP_BITS_TILED32_T,
+                              parity_ops_args(P, c->gens, ops, ws, 0, P.o_ctbits)),
+                "parity(C^T)");
     IQP_TRY(launch_bitflip_fwd(lc, BitflipFwdArgs{at<uint64_t>(ws, P.o_cbits), enc, P.l, P.mw,
                                                   mean ? mean : at<double>(ws, P.o_rowsum),
                                                   nullptr, stat}),

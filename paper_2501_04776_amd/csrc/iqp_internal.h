@@ -545,14 +545,13 @@ hipError_t launch_prep(const LaunchCtx &lc, const BitflipPrepArgs &a, const Supp
 hipError_t launch_support(const LaunchCtx &lc, const SupportArgs &a);
 hipError_t launch_row_perm(const LaunchCtx &lc, const RowPermArgs &a);
 // Parities in one layout, or of two row sets: (la, lb) one of (1, 1), (4, 4),
-// (0, 3), (1, 2).
+// (0, 3).
 hipError_t launch_parity(const LaunchCtx &lc, int layout, const ParityArgs &a);
 hipError_t launch_parity2(const LaunchCtx &lc, int la, const ParityArgs &a, int lb,
                           const ParityArgs &b);
 hipError_t launch_phase_fwd(const LaunchCtx &lc, int prec, int fm, int fn, const FwdArgs &a);
 hipError_t launch_epilogue(const LaunchCtx &lc, const EpiArgs &a);
 hipError_t launch_finalize(const LaunchCtx &lc, const FinArgs &a);
-hipError_t launch_coef_plain(const LaunchCtx &lc, const CoefArgs &a);
 hipError_t launch_weights(const LaunchCtx &lc, const WeightsArgs &a);
 hipError_t launch_gate_list(const LaunchCtx &lc, const GateListArgs &a);
 hipError_t launch_phase_bwd(const LaunchCtx &lc, int prec, int fm, int fn, const BwdArgs &a);

@@ -522,7 +522,6 @@ hipError_t launch_parity2(const LaunchCtx &lc, int la, const ParityArgs &a, int 
     if (la == 1 && lb == 1) return parity_pair<1, 1>(lc, a, b);
     if (la == 4 && lb == 4) return parity_pair<4, 4>(lc, a, b);
     if (la == 0 && lb == 3) return parity_pair<0, 3>(lc, a, b);
-    if (la == 1 && lb == 2) return parity_pair<1, 2>(lc, a, b);
     return hipErrorInvalidValue;
 }
 
