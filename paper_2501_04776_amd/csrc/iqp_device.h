@@ -253,7 +253,7 @@ __device__ __forceinline__ void finalize_store(const FinArgs &a, int64_t k, doub
     }
 }
 
-// Whether the FP32 forward goes over the non-zero entries of C (ChainGate).
+// Whether an FP32 call goes over the non-zero entries of C (ChainGate).
 __device__ __forceinline__ bool chain_on(const ChainGate &g) {
     return g.nnz && __builtin_amdgcn_readfirstlane((int)(gptr(g.nnz)[0] <= g.limit));
 }

@@ -61,11 +61,12 @@ constexpr int64_t kI8MaxSamplesPerUnit = (int64_t)1 << 16;
 // listed; heavier generators are read from their bit rows.
 constexpr int kSupCap = 8;
 
-// The FP32 forward has two ways to the same bits (the FP32 matrix product adds
-// one term at a time, in gate order, and adding a zero term changes nothing):
-// the matrix cores over all gates, or one addition per non-zero entry of C.
-// nnz counts C's entries on the device; at most `limit` of them take the
-// second way. NULL: always the matrix cores.
+// The FP32 passes have two ways to the same bits (the FP32 matrix product adds
+// one term at a time, in gate or sample order, and adding a zero term changes
+// nothing): the matrix cores over all entries of C, or one addition per non-zero
+// one. nnz counts C's entries on the device; at most `limit` of them take the
+// second way. NULL: always the matrix cores. All kernels of a pass read nnz, so
+// none of them may write where it lives.
 struct ChainGate {
     const unsigned long long *nnz = nullptr;
     unsigned long long limit = 0;
@@ -109,10 +110,6 @@ struct BitsliceArgs {
 };
 inline int64_t blocks_of(const BitsliceArgs &a) { return ceil_div(a.ldx * a.W, 4); }
 
-// Support lists of `rows` generators (m real ones, W words each; rows >= m
-// are written as weight 0): sup[j * kSupCap + k] = qubit of the k-th set bit
-// of generator j, -1 past its weight, and sup[j * kSupCap] = -2 for a
-// generator heavier than kSupCap.
 // Finds the observables of weight > 0 (RowPerm; *nrows must read 0).
 struct RowPermArgs {
     const uint64_t *ops;
@@ -122,6 +119,10 @@ struct RowPermArgs {
 };
 inline int64_t blocks_of(const RowPermArgs &a) { return ceil_div(a.l, 256); }
 
+// Support lists of `rows` generators (m real ones, W words each; rows >= m
+// are written as weight 0): sup[j * kSupCap + k] = qubit of the k-th set bit
+// of generator j, -1 past its weight, and sup[j * kSupCap] = -2 for a
+// generator heavier than kSupCap.
 struct SupportArgs {
     const uint64_t *gens;
     int64_t m;
@@ -359,7 +360,8 @@ inline int64_t blocks_of(const GateListArgs &a) {
 // the sample words) and the gradient partials gpart[ksplits][n_ob][m_pad],
 // n_ob = l_pad / (32 cf), written for the listed gates of each block only;
 // btbits / ctbits are the transposed word-major parities of the samples /
-// observables against the generators (word w of gate j at [w * m_pad + j]). Every split must hold >= 1 sample word.
+// observables against the generators (word w of gate j at [w * m_pad + j]). Every
+// split must hold >= 1 sample word.
 struct BwdArgs {
     const uint16_t *shi, *slo;
     const float *s32;

@@ -278,20 +278,6 @@ __device__ __forceinline__ void parity_bs_body(const ParityArgs &a, int64_t blk)
     }
 }
 
-// Parities straight from the rows. A block stages rw row words of every qubit
-// in LDS, Xs[q * st + i] = bit column q of row word i, by transposing the 64x64
-// blocks of its rows (a wave per block), a zero column last; then a lane takes
-// one generator of 64 and XORs the LDS words of its support, all rw words at
-// once. So neither the bit columns nor their gathers pass through memory: the
-// former kernels wrote the columns out and gathered 512 bytes per support
-// qubit from L2, with 64 registers of words per lane (two waves per SIMD), and
-// stored 16 bytes to each of 64 lines at a time. Here a lane's words of one
-// row word are adjacent over the lanes (layouts 4, 2), or after a transpose
-// over the rows (layouts 1, 0), so stores are 256- or 512-byte runs. Bound by
-// vector instructions (the transposes) and LDS gathers. Row-major C and B^T at
-// n = 300 (45150 generators, 1000 observables, 10^4 samples, 62 MB out), bit
-// columns included: 50 -> 24 us; at n = 1000 (10^5, 2000, 10^4; 150 MB): 107
-// -> 76 us; 10 qubits, 55 generators: 23 -> 7 us.
 // Transposes the N x N block that N adjacent lanes hold in N pieces of 16 bytes
 // (lane q, piece p) <-> (lane p, piece q), N = 2 or 4.
 template <int N>
@@ -338,6 +324,24 @@ __device__ __forceinline__ void store_rows(const uint64_t (&x)[RW], uint64_t IQP
                     p[q];
     }
 }
+
+// Parities straight from the rows. A block stages rw row words of every qubit
+// in LDS, Xs[q * st + i] = bit column q of row word i, by transposing the 64x64
+// blocks of its rows (a wave per block), a zero column last; then a lane takes
+// one generator of 64 and XORs the LDS words of its support, all rw words at
+// once. So neither the bit columns nor their gathers pass through memory: the
+// former kernels wrote the columns out and gathered 512 bytes per support
+// qubit from L2, with 64 registers of words per lane (two waves per SIMD), and
+// stored 16 bytes to each of 64 lines at a time. Here a lane's words of one
+// row word are adjacent over the lanes (layouts 4, 2), or after a transpose
+// over the rows (layouts 1, 0), so stores are 256- or 512-byte runs. Row-major C
+// and B^T at n = 300 (45150 generators, 1000 observables, 10^4 samples, 62 MB
+// out), bit columns included: 50 -> 24 us; at n = 1000 (10^5, 2000, 10^4; 150
+// MB): 107 -> 78 us; 10 qubits, 55 generators: 23 -> 7 us. Bound by how little
+// runs at once, not by a unit: a block's staging, gathers and stores follow one
+// another, two or three blocks fit a CU's LDS (1.5 to 1.9 waves per SIMD over
+// the run), and vector instructions issue on a third of the cycles, all
+// instructions on 50 to 60 %.
 
 // Stages the bit columns of row words rw0 .. rw0 + RW - 1 in Xs.
 template <int RW>
@@ -1184,8 +1188,8 @@ hipError_t launch_phase_fwd_persistent(const LaunchCtx &lc, int prec, int fm, in
 }
 
 // ---------------------------------------------------------------------------
-// epilogue: one block per (observable k, chunk of kEpiChunk samples).
-
+// epilogue: units of one observable k and one chunk of kEpiChunk samples.
+//
 // Bound by its vector instructions, about 45 per phase, 10 of them FP64, and by
 // reading E. kLanes = 256: a block per unit, which ends soonest where units are
 // few; 64: a wave per unit, whose indices and reduction then serve 16 phases
@@ -1505,16 +1509,17 @@ hipError_t launch_weights(const LaunchCtx &lc, const WeightsArgs &a) {
 // epilogue; the epilogue is a masked sum over the tile's observable rows and
 // one cross-lane add.
 //   A operand: S in the register image written by weights_kernel
-//   B operand: +-1 from the sample-contiguous B^T bits (transposed tiled32:
-//              row = gate j, bits over samples), K-step t of a sample word
-//              is byte 2t + h of the lane's word
-//   epilogue:  c_kj from the C^T bits (row = gate j, bits over observables)
+//   B operand: +-1 from the B^T bits, word-major (word w of gate j, 64 samples,
+//              at [w * m_pad + j]), one word per lane and listed gate; K-step t
+//              of a sample word is byte 2t + h of the lane's word
+//   epilogue:  c_kj from the C^T bits (word-major too, bits over observables)
 // A workgroup is 4 waves that share an observable block (the S strip,
-// staged through LDS per sample word, double-buffered) and take 4
-// consecutive gate blocks. Workgroups are ordered gate block fastest, so an
-// XCD's workgroups share one S strip in L2. As in the forward, the last
-// region of a word runs after the barrier that validates the next word's
-// buffer, so it already expands the next word's first K-step.
+// staged through LDS per sample word, double-buffered) and take 32 FN gates
+// each of one tile of the block's gate list. Units run observable block fastest
+// inside groups of blocks (bwd_unit). As in the forward, the last region of a
+// word runs after the barrier that validates the next word's buffer, so it
+// already expands the next word's first K-step.
+//
 // Gate lists (GateListArgs): one block per (observable block, kListSeg gates).
 // Each thread takes kListSeg / 256 gates, reads their C^T words for the
 // block, counts them per class; a block prefix sum and one atomic add per
@@ -2215,8 +2220,6 @@ __device__ __forceinline__ void bwd_i8_body(const BwdArgs &a, const BwdUnit &U, 
     bwd_store<FN>(gs, gt, h, gpart);
 }
 
-// The 64 x 64 wave tile fits two waves per SIMD (its INT32 accumulators in
-// VGPRs, no AGPRs), which hides the per-block barrier and load latency.
 // ---------------------------------------------------------------------------
 // FP16 + FP8 form of the backward (IQP_SPLIT_BF16_FP8). Row k of S is scaled
 // by 2^e_k and held as an FP16 limb plus an FP8 E4M3 limb (weights_kernel).
@@ -2449,6 +2452,9 @@ __device__ __forceinline__ void bwd_f16f8_body(const BwdArgs &a, const BwdUnit &
                                 gpart);
 }
 
+// The INT8 form's 64 x 64 wave tile fits two waves per SIMD (its INT32
+// accumulators in VGPRs, no AGPRs), which hides the per-block barrier and load
+// latency.
 template <int FN>
 constexpr int kI8Waves = FN == 2 ? 2 : 1;
 // Plain launches: units in block order. Blocks go to the XCDs round-robin, so
@@ -2978,11 +2984,12 @@ hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a) {
 // Partials per gate chunk and per observable chunk are added in order by the
 // finishing kernels. An absolute error of S_k is a relative one of e^{S_k}, and
 // S_k reaches the hundreds, so the partials of S_k are added with their rounding
-// carried along (add_exact) into the exponential. Bound by the vector
-// instructions of the transposes and of the walks over set bits, two blocks of
-// LDS per CU. 1000 qubits, 10^5 gates, 10^4 observables (1.1 % of C non-zero): C's
-// parities and the forward 81 + 210 -> 109 us, the gradient's and the gradient
-// 83 + 383 -> 99 us.
+// carried along (add_exact) into the exponential. 1000 qubits, 10^5 gates, 10^4
+// observables (1.1 % of C non-zero): C's parities and the forward 81 + 210 -> 112 +
+// 12 us, the gradient's and the gradient 83 + 383 -> 99 + 8 us. Bound by the
+// serial walks over set bits, whose lanes wait for the longest, with 1.3 waves
+// per SIMD over the run (two blocks of LDS per CU, 720 blocks): vector
+// instructions issue on 41 and 32 % of the cycles, all instructions on 57 and 52 %.
 constexpr double kDeep = -700.0, kTiny = 1e-300;
 
 // sum + err += x, with the rounding of the sum kept in err (Knuth's two-sum).

@@ -56,8 +56,8 @@ hipError_t launch_sparse_bound(const LaunchCtx &lc, const SparseBoundArgs &a) {
 }
 
 // Gradient by table lookup. A block takes observable k and kC (1 or 2) chunks
-// of kEpiChunk samples, each with tables of its own. Thread t computes S_ki for the four samples 4t .. 4t + 3
-// of the chunk and writes their 16 signed sums
+// of kEpiChunk samples, each with tables of its own. Thread t computes S_ki for
+// the four samples 4t .. 4t + 3 of the chunk and writes their 16 signed sums
 //   L_t[v] = sum_{b < 4} (-1)^{v_b} S_{k, c + 4t + b},  v = 0 .. 15,
 // so that, with v_t(j) the nibble of generator j's parity bits over those
 // four samples (bits 4t .. 4t + 3 of the chunk's parity words), the chunk's
@@ -112,8 +112,8 @@ __device__ __forceinline__ int block_excl_scan(int c, int *wsum, int *tot) {
 
 
 // The set bits of words w0 .. w1 - 1 of a row of C (word w: word(w)), in gate
-// order, into the LDS list lst, 256 row words at a time (a block prefix sum of their popcounts places
-// each word's bits); fill(n) runs on every full list (n = kLutList) and on
+// order, into the LDS list lst, 256 row words at a time (a block prefix sum of
+// their popcounts places each word's bits); fill(n) runs on every full list (n = kLutList) and on
 // the last, partial one (n may be 0), between barriers, so fill may read
 // lst and the block's other shared data freely.
 template <typename R, typename F>
@@ -312,11 +312,12 @@ __device__ __forceinline__ void sparse_bwd_lut_body(const SparseBwdArgs &a, int6
 //   E_ki = T_k - 2 sum_{j in J_k, b_ij = 1} t_j,  T_k = sum_{j in J_k} t_j (FP64),
 // with the FP32 sum folded modulo the float nearest pi every 32 generators
 // (the whole multiples kept in an exact count), then reduced modulo 2 pi in
-// FP64 as the dense epilogue does. Bound by the vector units: per sample and
-// 64 entries 20 instructions for the exchange, 24 for the offsets, 24 for the
-// sums and the fold (85 with a full 64x64 transpose per word, when n = 300,
-// 1000 observables, 10^4 samples took 0.309 ms and now 0.294; n = 1000, 10^5
-// gates, 2000 observables 1.02 and 0.92 ms).
+// FP64 as the dense epilogue does. Bound by the vector units, which issue on every
+// cycle (five waves per SIMD over the run): per sample and 64 entries 20
+// instructions for the exchange, 24 for the offsets, 24 for the sums and the fold
+// (85 with a full 64x64 transpose per word, when n = 300, 1000 observables, 10^4
+// samples took 0.309 ms and now 0.294; n = 1000, 10^5 gates, 2000 observables
+// 1.02 and 0.92 ms).
 template <bool kIndep>
 __device__ __forceinline__ void lut_fwd_words(const SparseFwdArgs &a, int64_t k, int64_t sw,
                                               int64_t j, u32x4 (&wv)[2]);
@@ -638,10 +639,12 @@ hipError_t launch_sparse_finish(const LaunchCtx &lc, const SparseFinishArgs &a) 
 // samples; the row of C is compacted into an LDS list as in the table-lookup
 // kernels, and per entry a wave loads one parity byte per lane (64 contiguous
 // bytes of B^T) and adds under its bits: a shift, a sign insert and an add per
-// term, against a matrix-core term for every entry of C, zero or not. Bound by
-// the vector units. n = 300, 517 observables, 2501 samples, C 1.3 % full:
-// 0.147 ms, the matrix-core kernel 1.95 ms (1.0e13 and, of all entries,
-// 3.0e13 terms/s).
+// term, against a matrix-core term for every entry of C, zero or not. n = 300,
+// 517 observables, 2501 samples, C 1.3 % full (7.7e8 non-zero terms): 0.148 ms, 5.2e12
+// terms/s; the matrix-core kernel 1.95 ms, 3.0e13 of all terms. The vector units
+// issue on 62 % of the cycles, 4.7 instructions a term; the rest is waiting for
+// the parity bytes with too little else to run, 2.6 waves per SIMD over the run:
+// the second block of an observable has 453 samples, one busy wave in four.
 __device__ __forceinline__ void count_body(const CountArgs &a, int64_t blk) {
     __shared__ double sh[256];
     const int64_t total = a.l_pad * a.mw;
@@ -777,8 +780,12 @@ hipError_t launch_chain_fwd(const LaunchCtx &lc, const ChainFwdArgs &a) {
 // four of them, and walks the samples with |S_ki| and the signs of 64 samples
 // read from LDS by all lanes at once. The T go to memory in row order; the
 // second kernel gives a lane a gate, finds each T by the row's entries before
-// the wave's 64 gates and a ballot, and adds them in the order above. Bound by
-// the vector units: three instructions per term.
+// the wave's 64 gates and a ballot, and adds them in the order above. At the
+// sizes above 0.099 ms, 7.8e12 terms/s, bound by the vector units, which issue on
+// 80 % of the cycles, 4 instructions a term (three for the term, the rest for
+// the weights, which every block of a row computes), and 0.033 ms for the sums
+// (vector instructions on 30 % of the cycles: the scalar work per row and the
+// latency of the loads).
 __device__ __forceinline__ void rank_body(const RankArgs &a, int64_t k) {
     __shared__ int wsum[2][4];
     const glb<const uint64_t> row = gptr(a.crm) + k * a.mw;
