@@ -978,7 +978,8 @@ static int run_bitflip(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
     double *enc = at<double>(ws, P.o_enc), *stat = at<double>(ws, P.o_stat);
     IQP_TRY(launch_prep(lc, BitflipPrepArgs{c->theta, P.m, enc}, support_args(P, c->gens, ws)),
             "bitflip_prep, support");
-    const ParityArgs pc = parity_ops_args(P, c->gens, ops, ws, P.l_pad, P.o_cbits);
+    const ParityArgs pc =
+        bitflip_blocking(parity_ops_args(P, c->gens, ops, ws, P.l_pad, P.o_cbits));
     if (pc.rw) {
         // the sums take the space of C, the dot products that of C^T
         const int64_t ngc = ceil_div(pc.Gw, pc.gpb);
