@@ -73,16 +73,23 @@ hipError_t launch_sparse_bound(const LaunchCtx &lc, const SparseBoundArgs &a) {
 // never conflict.
 constexpr int kLutTables = (int)(kEpiChunk / 4);  // one per thread of the block
 constexpr int kLutList = 1024;                    // generators per list fill
-// Gradient blocks take two chunks of samples once that leaves kPairBlocks of
-// them: half the atomics into the gates' sums, which bound the kernel once the
-// parity rows outgrow an L2, and half the compactions. Whole gradients with two
-// and with one chunk a block: n = 300, 40000 gates, 10^4 samples 0.114 and
-// 0.154 ms at 400 observables, 0.301 and 0.420 at 1600; n = 1000, 10^5 gates
-// 1.16 and 1.99 ms. With fewer blocks than the chip runs at once the longer
-// ones are the time: 1.03 to 1.3 times it at 200 blocks and under, 0.81 to
-// 0.96 at 400. Three chunks a block (tables of 48 KB) took 0.90 to 1.06 of the
-// time of two, four 1.00 to 1.27.
-constexpr int64_t kPairBlocks = 320;
+// Over shared samples, gradient blocks take two chunks once that leaves
+// kPairBlocks of them: half the atomics into the gates' sums, which bound the
+// kernel once the parity rows outgrow an L2, and half the compactions. Whole
+// gradients with two and with one chunk a block: n = 300, 40000 gates, 10^4 samples
+// 0.301 and 0.420 ms at 1600 observables; n = 1000, 10^5 gates 1.16 and 1.99 ms.
+// With few blocks the longer ones are the time, and where the chunks are odd in
+// number half of the blocks are half as long, so the line is twice as high there.
+// Over 230 shapes of 50 to 7000 observables and 2 to 10 chunks, two chunks took
+// 0.57 to 1.10 of the time of one past the line (0.82 in the mean; over 1.03 in
+// eight shapes, whose rows of C have some ten entries), 0.81 to 1.23 from 320
+// blocks to the line and 0.94 to 1.50 below. Three chunks a block (tables of 48
+// KB) took 0.90 to 1.06 of the time of two, four 1.00 to 1.27.
+//
+// Independent sets read every observable's own bit columns, wait for them more
+// than for anything else, and lose waves to the larger tables: two chunks took
+// more time than one, up to 1.4 and more, in 164 of 214 shapes, so they take one.
+constexpr int64_t kPairBlocks = 640;
 
 static_assert(kLutTables == 256, "one table per thread of a 256-thread block");
 
@@ -586,22 +593,15 @@ hipError_t launch_sparse_fwd(const LaunchCtx &lc, const SparseFwdArgs &a) {
     return e;
 }
 
-template <int kC>
+template <bool kIndep, int kC>
 static void launch_bwd_lut(const LaunchCtx &lc, const SparseBwdArgs &a) {
     const int64_t units = a.l * ceil_div(a.s, kC * kEpiChunk);
     const unsigned blocks = (unsigned)lut_grid(units);
-    const bool strided = (int64_t)blocks < units;
-    if (a.bsrc.xt && strided)
-        hipLaunchKernelGGL((sparse_bwd_lut_kernel<true, true, kC>), dim3(blocks), dim3(256), 0,
-                           lc.stream, a, units);
-    else if (a.bsrc.xt)
-        hipLaunchKernelGGL((sparse_bwd_lut_kernel<true, false, kC>), dim3(blocks), dim3(256), 0,
-                           lc.stream, a, units);
-    else if (strided)
-        hipLaunchKernelGGL((sparse_bwd_lut_kernel<false, true, kC>), dim3(blocks), dim3(256), 0,
+    if ((int64_t)blocks < units)
+        hipLaunchKernelGGL((sparse_bwd_lut_kernel<kIndep, true, kC>), dim3(blocks), dim3(256), 0,
                            lc.stream, a, units);
     else
-        hipLaunchKernelGGL((sparse_bwd_lut_kernel<false, false, kC>), dim3(blocks), dim3(256), 0,
+        hipLaunchKernelGGL((sparse_bwd_lut_kernel<kIndep, false, kC>), dim3(blocks), dim3(256), 0,
                            lc.stream, a, units);
 }
 
@@ -609,10 +609,13 @@ hipError_t launch_sparse_bwd(const LaunchCtx &lc, const SparseBwdArgs &a) {
     if (a.l <= 0 || a.s <= 0) return hipSuccess;
     hipEvent_t ev;
     timed_begin(lc, KF_BWD, &ev);
-    if (a.l * ceil_div(a.s, 2 * kEpiChunk) >= kPairBlocks)
-        launch_bwd_lut<2>(lc, a);
+    const int64_t chunks = ceil_div(a.s, kEpiChunk);
+    if (a.bsrc.xt)
+        launch_bwd_lut<true, 1>(lc, a);
+    else if (chunks > 1 && a.l * ceil_div(chunks, 2) >= kPairBlocks * (1 + chunks % 2))
+        launch_bwd_lut<false, 2>(lc, a);
     else
-        launch_bwd_lut<1>(lc, a);
+        launch_bwd_lut<false, 1>(lc, a);
     hipError_t e = hipGetLastError();
     timed_end(lc, KF_BWD, ev);
     return e;
