@@ -385,9 +385,10 @@ struct BwdShape {
 };
 BwdShape bwd_shape(int prec, int bfm, int bfn);
 // Workgroup tiles over one block's gate lists: room for every gate, and for
-// the partly filled last tile of each further class.
+// the partly filled last tile of each further class (gates that fit one tile
+// never take more).
 __host__ __device__ inline int64_t bwd_list_tiles(int64_t m_pad, int fn, bool split) {
-    return ceil_div(m_pad, 128 * fn) + (split ? 2 : 0);
+    return ceil_div(m_pad, 128 * fn) + (split && m_pad > 128 * fn ? 2 : 0);
 }
 inline int64_t bwd_units(const BwdArgs &a, int prec, int bfm, int bfn) {
     const BwdShape sh = bwd_shape(prec, bfm, bfn);

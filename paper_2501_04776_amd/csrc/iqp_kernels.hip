@@ -1649,44 +1649,60 @@ hipError_t launch_gate_list(const LaunchCtx &lc, const GateListArgs &a) {
 }
 
 // The list tile t of observable block ob: the parts (halves of the block) its
-// gates need, and where its entries are: entry i of the tile, i < n, at
-// L[sign i]. Tiles of class 0 hold kT0 gates, the others kT1. False,
-// uniformly over the workgroup, when the block's lists have no tile t.
+// gates need, and its entries first .. first + n - 1 (of which a tile takes
+// its size) of the block's classes 0, 1 and 2 one after the other. False,
+// uniformly over the workgroup, when the block's lists have no tile t. Tiles of
+// class 0 hold kT0 gates, the others kT1 and half of the block; where few gates
+// are listed, tiles that hold every class and run the whole block cost less
+// than a partly filled tile of each class. Up to kT0 gates so take one tile.
 struct ListTile {
     const int32_t IQP_GLOBAL *L;
-    int n, sign;
+    int64_t m_pad;
+    int c0, c01, first, n;
     uint32_t parts;
     template <int kT0, int kT1, bool kSplit>
     __device__ __forceinline__ bool find(const BwdArgs &a, int64_t ob, int64_t t) {
         const int32_t IQP_GLOBAL *cnt = gptr(a.gcnt) + ob * 4;
         L = gptr(a.glist) + ob * 2 * a.m_pad;
-        int total = __builtin_amdgcn_readfirstlane(cnt[0]);
-        const int tiles = (total + kT0 - 1) / kT0;
+        m_pad = a.m_pad;
+        c0 = __builtin_amdgcn_readfirstlane(cnt[0]);
+        c01 = c0;
+        int tiles = (c0 + kT0 - 1) / kT0;
         parts = kSplit ? 3u : 1u;
-        sign = 1;
-        if (t < tiles) {
-            L += t * kT0;
-            n = total - (int)t * kT0;
-            return true;
+        if (kSplit) {
+            const int c1 = __builtin_amdgcn_readfirstlane(cnt[1]);
+            const int c2 = __builtin_amdgcn_readfirstlane(cnt[2]);
+            c01 = c0 + c1;
+            const int tiles1 = (c1 + kT1 - 1) / kT1, tiles2 = (c2 + kT1 - 1) / kT1;
+            const int together = (c01 + c2 + kT0 - 1) / kT0;
+            // (one tile of a class other than 0 alone costs less than one of all)
+            if (together * 2 * kT0 + (together > 1) <= tiles * 2 * kT0 + (tiles1 + tiles2) * kT1) {
+                if (t >= together) return false;
+                first = (int)t * kT0;
+                n = c01 + c2 - first;
+                return true;
+            }
+            if (t >= tiles) {
+                t -= tiles;
+                const bool upper = t >= tiles1;
+                if (upper) t -= tiles1;
+                if (t >= tiles2 && upper) return false;
+                parts = upper ? 2u : 1u;
+                first = (upper ? c01 : c0) + (int)t * kT1;
+                n = (upper ? c2 : c1) - (int)t * kT1;
+                return true;
+            }
+        } else if (t >= tiles) {
+            return false;
         }
-        if (!kSplit) return false;
-        t -= tiles;
-        total = __builtin_amdgcn_readfirstlane(cnt[1]);
-        const int tiles1 = (total + kT1 - 1) / kT1;
-        if (t < tiles1) {
-            parts = 1u;
-            L += a.m_pad + t * kT1;
-            n = total - (int)t * kT1;
-            return true;
-        }
-        t -= tiles1;
-        total = __builtin_amdgcn_readfirstlane(cnt[2]);
-        if (t >= (total + kT1 - 1) / kT1) return false;
-        parts = 2u;
-        sign = -1;
-        L += 2 * a.m_pad - 1 - t * kT1;
-        n = total - (int)t * kT1;
+        first = (int)t * kT0;
+        n = c0 - first;
         return true;
+    }
+    // gate of entry first + i (see GateListArgs for the classes' places)
+    __device__ __forceinline__ int32_t gate(int i) const {
+        const int e = first + i;
+        return L[e < c0 ? (int64_t)e : e < c01 ? m_pad + (e - c0) : 2 * m_pad - 1 - (e - c01)];
     }
 };
 
@@ -1699,7 +1715,7 @@ struct GateTile {
 #pragma unroll
         for (int g = 0; g < FN; ++g) {
             const int pos = (wave_id() * FN + g) * 32 + r;
-            j[g] = pos < t.n ? t.L[t.sign * pos] : -1;
+            j[g] = pos < t.n ? t.gate(pos) : -1;
         }
     }
     // the gate whose words column block g reads (gate 0 past the list's end)
@@ -1718,7 +1734,9 @@ __device__ __forceinline__ uint64_t gate_word(const uint64_t IQP_GLOBAL *row, ui
 // the observable blocks run in groups of `grp`; inside a group the observable
 // block changes fastest, so workgroups that run at the same time share both
 // their S strips (grp of them) and their B^T columns. The last group may be
-// smaller.
+// smaller. Units that run all at once take the first tiles of every block first:
+// these hold gates, the last ones mostly none, and a mixed order puts two units
+// with gates on one CU while others have none.
 struct BwdUnit {
     int64_t ob, t, ks;
 };
@@ -1728,7 +1746,7 @@ __device__ __forceinline__ BwdUnit bwd_unit(int64_t gu, int64_t n_ob, int64_t ti
     const int64_t per_split = n_ob * tiles;
     U.ks = gu / per_split;
     const int64_t u = gu - U.ks * per_split;
-    const int64_t G = grp < 1 ? 1 : (grp > n_ob ? n_ob : grp);
+    const int64_t G = per_split <= 1024 || grp > n_ob ? n_ob : grp < 1 ? 1 : grp;
     const int64_t g = u / (G * tiles);
     const int64_t gsz = (g + 1) * G <= n_ob ? G : n_ob - g * G;
     const int64_t r = u - g * G * tiles;
