@@ -7,6 +7,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <utility>
 #include <vector>
@@ -516,30 +517,44 @@ static int run_sparse_parities(const Plan &P, const iqp_circuit *c, const uint64
 // (2^31 terms: about 35 us of matrix cores against 10 us for the count and the
 // kernels that leave at once).
 constexpr double kChainTerms = 2147483648.0;
-// It goes over the non-zero entries up to this share of them: the matrix cores
-// take 6e13 terms/s, whatever C holds, when their wave tiles fill the chip, the
-// other way 5 to 7e12 non-zero terms/s at any size. Where the tiles leave wave
-// slots empty the line moves up, to at most a third (256 observables, 4096
-// samples, 20000 gates: 1.74 ms of matrix cores on 192 of 1024 slots, 0.23 ms
-// for 7.7 % non-zero).
-static double chain_density(const Plan &P) {
-    const int64_t tiles = (P.l_pad / (32 * P.tc.fm)) * (P.s_pad / (32 * P.tc.fn)) * P.tc.splits;
-    const double fill = (double)tiles / (double)(ceil_div(tiles, kWaveSlots) * kWaveSlots);
-    const double d = 1.0 / (12.0 * fill);
-    return d < 1.0 / 3.0 ? d : 1.0 / 3.0;
-}
-
-// Launches the forward contraction. No element's arithmetic depends on the wave
-// tile, so a product whose 128 x 128 tiles would fill less than half of the
-// wave slots runs in 64 x 64 ones, four times as many waves of a quarter of
+// Wave tile of the forward contraction, in 32-blocks. No element's arithmetic
+// depends on it, so a product whose 128 x 128 tiles would fill less than half of
+// the wave slots runs in 64 x 64 ones, four times as many waves of a quarter of
 // the length (150 observables, 600 samples, 700 gates, split3-BF16: 38 -> 14
 // us); the splits stay those of the plan's tile.
-static hipError_t launch_fwd(const LaunchCtx &lc, const Plan &P, const FwdArgs &a) {
-    int fm = P.tc.fm, fn = P.tc.fn;
+static void fwd_tile(const Plan &P, int &fm, int &fn) {
+    fm = P.tc.fm;
+    fn = P.tc.fn;
     if (fm == 4 && fn == 4 &&
         2 * (P.l_pad / 128) * (P.s_pad / 128) * P.tc.splits <= kWaveSlots && !P.tc.fixed_fwd)
         fm = fn = 2;
+}
+
+static hipError_t launch_fwd(const LaunchCtx &lc, const Plan &P, const FwdArgs &a) {
+    int fm, fn;
+    fwd_tile(P, fm, fn);
     return launch_phase_fwd(lc, P.prec, fm, fn, a);
+}
+
+// The FP32 forward goes over the non-zero entries up to as many as take the
+// matrix cores' time, at most a third of them. A matrix-core wave of a
+// 128 x 128 tile takes 17.3 us for a gate word (64 x 64: 5.2), one wave to a SIMD,
+// whatever C holds: 6e13 terms/s with every slot filled, but the whole length of
+// a split with few tiles. The other way a wave takes 0.1 us for an entry of its
+// observable and 512 samples, one entry of a row after the other, and from a wave
+// per SIMD on 0.08 to 0.125 us of a SIMD's time. 52 observables, 500 samples, 10^5
+// gates: 0.62 ms of matrix cores, 0.53 ms for 5 % non-zero and 1.28 ms for 13 %;
+// 517, 2501, 45150: 1.95 and, for 1.3 %, 0.15 ms.
+static unsigned long long chain_limit(const Plan &P) {
+    int fm, fn;
+    fwd_tile(P, fm, fn);
+    const int64_t tiles = (P.l_pad / (32 * fm)) * (P.s_pad / (32 * fn)) * P.tc.splits;
+    const double word = 17.3 * fm * fn / 16.0 * (fm * fn < 16 ? 1.2 : 1.0);
+    const double matrix_us =
+        word * (double)ceil_div(tiles, kWaveSlots) * (double)ceil_div(P.mw, P.tc.splits);
+    const double entry_us = std::max(0.1 / (double)P.l,
+                                     0.125 * (double)ceil_div(P.s, 512) / (double)kWaveSlots);
+    return (unsigned long long)std::min((double)P.l * (double)P.m / 3.0, matrix_us / entry_us);
 }
 
 static int run_forward_fp32(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
@@ -549,7 +564,7 @@ static int run_forward_fp32(const Plan &P, const iqp_circuit *c, const uint64_t 
     // used
     ChainGate gate;
     gate.nnz = at<unsigned long long>(ws, P.o_nnz);
-    gate.limit = (unsigned long long)(chain_density(P) * (double)P.l * (double)P.m);
+    gate.limit = chain_limit(P);
     ThetaArgs th = theta_args(P, c->theta, ws);
     th.nnz = at<unsigned long long>(ws, P.o_nnz);
     IQP_TRY(launch_prep(lc, th, support_args(P, c->gens, ws)), "theta_prep, support");
@@ -661,8 +676,8 @@ static int run_backward(const Plan &P, const iqp_circuit *c, const uint64_t *ops
     GateListArgs la = gate_list_args(P, ws, P.tc.bfm, P.tc.bfn);
     BwdArgs ba = bwd_args(P, ws);
     GradArgs ga = grad_args(P, ws, P.tc.bfm, grad_theta);
-    // FP32: the non-zero entries of C alone where they are few (chain_density
-    // at full wave slots), at most cap to a row. C row-major takes the space of
+    // FP32: the non-zero entries of C alone where they are at most a twelfth (the
+    // matrix cores' 6e13 terms/s against 5 to 8e12), at most cap to a row. C row-major takes the space of
     // the gate lists, the ranks that of the gradient partials and T that of the
     // weights, each of which the other way writes after the count or not at all.
     // Its kernels take a block per observable and split, which one grid holds up
