@@ -400,44 +400,60 @@ __device__ __forceinline__ void parity_gather(const ParityArgs &a, int64_t gb, i
     if (!heavy) return;
     const uint64_t IQP_GLOBAL *rows = gptr(a.gens) + gb * 64 * W;
     if constexpr (RW <= 2) {
-        // Few of them in rows of many words: the wave takes each in turn, a lane
-        // per word, one load's latency instead of W / 8. 5000 qubits, 10^5
-        // generators of mean weight 3, 3867 rows: 104 us, a lane per generator
-        // 176 (eight words in flight), the bit-column kernels 125.
-        if (__popcll(heavy) * 8 <= W) {
-            for (uint64_t h = heavy; h; h &= h - 1) {
-                const int g = __builtin_ctzll(h);  // uniform over the wave
-                uint64_t p[RW];
+        // Few of them in rows of many words: the wave takes four at a time, a lane
+        // per word, one load's latency instead of W / 8 for each. 5000 qubits, 10^5
+        // generators, 3867 rows: 99 us at mean weight 3 and 287 at 6; a lane per
+        // generator 176 and 464, the bit-column kernels 125 and 320.
+        if (__popcll(heavy) * 4 <= W) {
+            for (uint64_t h = heavy; h;) {
+                int gi[4];  // uniform over the wave
+                uint64_t ws[4][2];
 #pragma unroll
-                for (int i = 0; i < RW; ++i) p[i] = 0ull;
-                for (int w = lane; w < W; w += 64) {
-                    uint64_t bits = rows[g * W + w];
-                    while (bits) {
-                        const uint64_t *col = Xs + (w * 64 + __builtin_ctzll(bits)) * ST;
-                        bits &= bits - 1;
-#pragma unroll
-                        for (int i = 0; i < RW; ++i) p[i] ^= col[i];
-                    }
+                for (int q = 0; q < 4; ++q) {  // the rows of four in flight
+                    gi[q] = h ? __builtin_ctzll(h) : -1;
+                    h &= h - 1;
+                    const uint64_t IQP_GLOBAL *row = rows + (gi[q] < 0 ? 0 : gi[q]) * W;
+                    ws[q][0] = gi[q] >= 0 && lane < W ? row[lane] : 0ull;
+                    ws[q][1] = gi[q] >= 0 && lane + 64 < W ? row[lane + 64] : 0ull;
                 }
 #pragma unroll
-                for (int i = 0; i < RW; ++i) {
+                for (int q = 0; q < 4; ++q) {
+                    if (gi[q] < 0) break;
+                    uint64_t p[RW];
 #pragma unroll
-                    for (int st = 32; st >= 1; st >>= 1)
-                        p[i] ^= (uint64_t)__shfl_xor((unsigned long long)p[i], st, 64);
-                    x[i] = lane == g ? p[i] : x[i];
+                    for (int i = 0; i < RW; ++i) p[i] = 0ull;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        uint64_t bits = ws[q][e];
+                        while (bits) {
+                            const uint64_t *col =
+                                Xs + ((lane + 64 * e) * 64 + __builtin_ctzll(bits)) * ST;
+                            bits &= bits - 1;
+#pragma unroll
+                            for (int i = 0; i < RW; ++i) p[i] ^= col[i];
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < RW; ++i) {
+#pragma unroll
+                        for (int st = 32; st >= 1; st >>= 1)
+                            p[i] ^= (uint64_t)__shfl_xor((unsigned long long)p[i], st, 64);
+                        x[i] = lane == gi[q] ? p[i] : x[i];
+                    }
                 }
             }
             return;
         }
     }
-    if (sv[0] == -2) {  // eight words in flight
+    if (sv[0] == -2) {
+        constexpr int kFly = RW <= 4 ? 8 : 1;  // words in flight, of 18 and more
         const uint64_t IQP_GLOBAL *row = rows + lane * W;
-        for (int w0 = 0; w0 < W; w0 += 8) {
-            uint64_t ws[8];
+        for (int w0 = 0; w0 < W; w0 += kFly) {
+            uint64_t ws[kFly];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) ws[q] = w0 + q < W ? row[w0 + q] : 0ull;
+            for (int q = 0; q < kFly; ++q) ws[q] = w0 + q < W ? row[w0 + q] : 0ull;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
+            for (int q = 0; q < kFly; ++q) {
                 uint64_t bits = ws[q];
                 while (bits) {
                     const uint64_t *col = Xs + ((w0 + q) * 64 + __builtin_ctzll(bits)) * ST;

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("words", [31, 32, 63, 64, 65, 127])
-@pytest.mark.parametrize("heavy", [1, 3, 4, 7, 8, 15, 16, 64])  # of every 64 generators
+@pytest.mark.parametrize("heavy", [1, 3, 4, 7, 8, 9, 15, 16, 17, 31, 32, 64])  # of every 64 generators
 def test_parity_heavy_generators(words, heavy):
     R, C = 200, 300
     n = 64 * words - 3
