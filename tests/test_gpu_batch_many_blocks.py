@@ -1,5 +1,6 @@
-"""GPU: a batch whose parities take more blocks than one grid holds (rows of 64
-words and more have a block per 64 rows and 256 gates): several launches."""
+"""GPU: a batch of so many circuits that their parities, cut into the blocks that
+one circuit alone takes (64 rows of 64 words and more, 256 gates), would take
+more of them than one grid holds."""
 import pytest
 import torch
 
