@@ -256,7 +256,10 @@ struct RankArgs {
     uint32_t *rank;
     unsigned long long *nnz;
 };
-inline int64_t blocks_of(const RankArgs &a) { return a.l; }
+// (a wave per row; the counter takes one atomic add per block)
+__host__ __device__ inline int64_t blocks_of(const RankArgs &a) {
+    return a.l < 4096 ? ceil_div(a.l, 4) : 1024;
+}
 // T[(ks l + k) cap + position of gate j in row k] = the sum over the samples of
 // split ks of S_ki (-1)^{b_ij}.
 struct ChainBwdArgs {
