@@ -3061,8 +3061,8 @@ hipError_t launch_bitflip_grad(const LaunchCtx &lc, const BitflipGradArgs &a) {
 // finishing kernels. An absolute error of S_k is a relative one of e^{S_k}, and
 // S_k reaches the hundreds, so the partials of S_k are added with their rounding
 // carried along (add_exact) into the exponential. 1000 qubits, 10^5 gates, 10^4
-// observables (1.1 % of C non-zero): C's parities and the forward 81 + 210 -> 112 +
-// 12 us, the gradient's and the gradient 83 + 383 -> 99 + 8 us. Bound by the
+// observables (1.1 % of C non-zero): C's parities and the forward 81 + 210 -> 110 +
+// 5 us, the gradient's and the gradient 83 + 383 -> 98 + 5 us. Bound by the
 // serial walks over set bits, whose lanes wait for the longest, with 1.3 waves
 // per SIMD over the run (two blocks of LDS per CU, 720 blocks): vector
 // instructions issue on 41 and 32 % of the cycles, all instructions on 57 and 52 %.
