@@ -219,11 +219,23 @@ __device__ __forceinline__ void sparse_bwd_lut_body(const SparseBwdArgs &a, int6
     const int64_t cg = blk / a.l, k = blk - cg * a.l, ch0 = cg * kC;
     const int64_t left = ceil_div(a.s, kEpiChunk) - ch0;
     const int nc = left < kC ? (int)left : kC;
-    if (weight_zero(a.bsrc, k)) return;
     const int tid = threadIdx.x, lane = tid & 63;
     __shared__ __attribute__((aligned(16))) float tab[kC * kLutTables * 16];
     __shared__ int32_t lst[kLutList];
     __shared__ int wsum[2][4];
+
+    // all phases in flight at once, before anything waits: with two chunks a block
+    // four waves run per SIMD, too few for one load after the other (1000 qubits and
+    // gates, 10^4 observables and samples: gradient 549 -> 495 us, one chunk 502)
+    float ph[kC][4];
+#pragma unroll
+    for (int c = 0; c < kC; ++c)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int64_t i = (ch0 + c) * kEpiChunk + 4 * tid + b;
+            ph[c][b] = gptr(a.phase)[k * a.s + (i < a.s ? i : a.s - 1)];
+        }
+    if (weight_zero(a.bsrc, k)) return;
 
     // the tables of these chunks
     const double al = gptr(a.coef)[2 * k], be = gptr(a.coef)[2 * k + 1];
@@ -236,7 +248,7 @@ __device__ __forceinline__ void sparse_bwd_lut_body(const SparseBwdArgs &a, int6
             float v = 0.0f;
             if (i < a.s) {
                 float sn, cs;
-                sincosf(gptr(a.phase)[k * a.s + i], &sn, &cs);
+                sincosf(kC > 1 && c > 0 ? ph[kC - 1][b] : ph[0][b], &sn, &cs);
                 v = (float)((al + be * (double)cs) * (double)sn);
             }
             S[b] = v;
