@@ -623,9 +623,10 @@ static int run_forward(const Plan &P, const iqp_circuit *c, const uint64_t *ops,
     // from the size on where the product takes well over the extra launch
     // (2^34 terms, 40 us). The row table lives in the row sums, which finalize
     // writes when there is more than one chunk.
-    const bool drop = P.mmd && P.prec != IQP_FP32 && pc.rw && P.nchunk > 1 &&
+    const bool drop = P.mmd && P.prec != IQP_FP32 && P.W < kColumnWords && P.nchunk > 1 &&
                       (double)P.l * (double)P.s * (double)P.m >= 17179869184.0;
     if (drop) {
+        pc = parity_from_rows(pc);
         int32_t *nrows = at<int32_t>(ws, P.o_rowsum), *pos = nrows + 2, *perm = pos + P.l;
         th.nnz = reinterpret_cast<unsigned long long *>(nrows);
         pc.perm = RowPerm{perm, pos, nrows};

@@ -236,6 +236,12 @@ static void build_table(const iqp_batch_plan *bp, int pass, const iqp_problem *p
             par.push_back(parity_ct_args(P, g, ops, base(p)));
         }
     }
+    // (the waves that decide for bit columns in memory are those of all problems)
+    int64_t waves = 0;
+    for (auto &a : par)
+        if (a.W >= 64) waves += a.Gw * ceil_div(a.Rw, 64);
+    for (auto &a : par)
+        if (a.W >= 64 && waves >= kColumnWaves) a.rw = 0;
     // Each problem's parities are cut into blocks that fill the chip alone; where
     // all of them make more, a block takes more generators for its staged rows.
     // Five circuits of 6791 qubits, 17575 gates, 75 observables, 3504 samples:

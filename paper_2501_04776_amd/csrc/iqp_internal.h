@@ -138,8 +138,8 @@ inline int64_t blocks_of(const SupportArgs &a) { return ceil_div(a.rows, 256); }
 // tiled32), 3 (transposed row-major) or 4 (transposed word-major); Gw = output
 // words per row in layouts 0/1, generator words in the others.
 // A block of the kernel takes rw row words and 64 gpb generators; from
-// kColumnWords words per row on, rw is 0 and the kernel reads the bit columns
-// Xt (ldx words each) that launch_parity makes first.
+// kColumnWords words per row on, and where kColumnWaves says so, rw is 0 and the
+// kernel reads the bit columns Xt (ldx words each) that launch_parity makes first.
 constexpr int kBitsWordMajor = 4;
 constexpr int kColumnWords = 128;
 struct ParityArgs {
@@ -172,11 +172,26 @@ inline int64_t parity_gpb(int64_t Gw, int64_t Rw, int rw) {
     const int64_t want = ceil_div(Gw * ceil_div(Rw, rw), 768);
     return want < 4 ? 4 : want > 64 ? 64 : round_up(want, 4);
 }
+// The parities of rows of 64 words and more (one row word a block, stored a word at
+// a time) lose to the bit columns in memory once these kernels' waves, one for 64
+// generators and 64 row words, fill the SIMDs: at 10^4 rows, 10^5 generators and 4100
+// to 8100 qubits C and B^T row-major at mean weight 3 take 430 us from LDS and 360
+// from columns, layouts 0 to 2 at mean weight 20 1.0 to 3.8 times as long (at 3 0.7 to
+// 0.9 times). With 939 waves and fewer LDS takes 0.05 to 0.9 times at most weights.
+constexpr int64_t kColumnWaves = 1024;
 inline ParityArgs parity_args(const uint64_t *rows, int64_t R, const uint64_t *gens,
                               const int32_t *sup, int64_t m, int W, uint64_t *Xt, int64_t ldx,
                               int64_t Rw, int64_t R_out, int64_t Gw, uint64_t *out) {
     ParityArgs a{rows, R, gens, sup, m, W, Xt, ldx, Rw, R_out, Gw, out, parity_rw(W), 4};
+    if (W >= 64 && Gw * ceil_div(Rw, 64) >= kColumnWaves) a.rw = 0;
     if (a.rw) a.gpb = parity_gpb(Gw, Rw, a.rw);
+    return a;
+}
+// The same from LDS at any number of waves (bitflip circuits, and forwards that leave
+// rows out).
+inline ParityArgs parity_from_rows(ParityArgs a) {
+    a.rw = parity_rw(a.W);
+    if (a.rw) a.gpb = parity_gpb(a.Gw, a.Rw, a.rw);
     return a;
 }
 inline int64_t blocks_of(const ParityArgs &a) {
@@ -446,6 +461,7 @@ inline int64_t blocks_of(const BitflipGradArgs &a) { return ceil_div(a.m, 256); 
 // qubits, 10^5 gates, 300 observables 134 and 159 -> 36 and 58 us, with the
 // finishing step's share below.
 inline ParityArgs bitflip_blocking(ParityArgs a) {
+    a = parity_from_rows(a);
     while (a.rw > 1 && (a.rw >= 2 * a.Rw || blocks_of(a) < 256)) {
         a.rw /= 2;
         a.gpb = parity_gpb(a.Gw, a.Rw, a.rw);
