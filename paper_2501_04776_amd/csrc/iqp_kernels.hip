@@ -401,9 +401,10 @@ __device__ __forceinline__ void parity_gather(const ParityArgs &a, int64_t gb, i
     const uint64_t IQP_GLOBAL *rows = gptr(a.gens) + gb * 64 * W;
     if constexpr (RW <= 2) {
         // Few of them in rows of many words: the wave takes four at a time, a lane
-        // per word, one load's latency instead of W / 8 for each. 5000 qubits, 10^5
-        // generators, 3867 rows: 99 us at mean weight 3 and 287 at 6; a lane per
-        // generator 176 and 464, the bit-column kernels 125 and 320.
+        // per word, one load's latency instead of W / 8 for each. 4000 qubits, 10^5
+        // generators, 3867 rows, row-major: 102 us at mean weight 3 and 304 at 6; with
+        // a lane per generator, a word at a time, 198 and 732, from bit columns in
+        // memory 136 and 301.
         if (__popcll(heavy) * 4 <= W) {
             for (uint64_t h = heavy; h;) {
                 int gi[4];  // uniform over the wave
